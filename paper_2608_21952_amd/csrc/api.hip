@@ -93,11 +93,13 @@ Plan plan_workspace(const ssdi8_dims* d) {
 }
 
 struct Fp16Plan {
-  size_t bT, c16, S, pin, cb, dec, total;
+  size_t bT, c16, S, pin, cbmax, cb, dec, total;
 };
 
-// FP16-baseline workspace: fp16 B^T and C fragments per chunk, fp32 chunk states and entering
-// states (fragment order), fp32 causal CB blocks, fp32 per-chunk decays.
+// FP16-baseline workspace: fp16 B^T and C fragments per chunk, fp32 chunk states and fp16 entering
+// states (fragment order), fp32 causal CB blocks and their absolute maxima, fp32 per-chunk
+// decays.  The entering states' region is sized for 4 bytes per element; the maxima (144 bytes
+// per (b, c, g)) take the start of its second half (16 KB per (b, c, h), H >= G).
 Fp16Plan plan_fp16(const ssdi8_dims* d) {
   const size_t B = (size_t)d->batch, L = (size_t)d->seqlen, H = (size_t)d->nheads;
   const size_t P = (size_t)d->headdim, G = (size_t)d->ngroups, N = (size_t)d->dstate;
@@ -107,7 +109,9 @@ Fp16Plan plan_fp16(const ssdi8_dims* d) {
   p.bT = off;  off = round_up(off + 2 * B * L * G * N, 256);
   p.c16 = off; off = round_up(off + 2 * B * L * G * N, 256);
   p.S = off;   off = round_up(off + 4 * B * nc * H * P * N, 256);
-  p.pin = off; off = round_up(off + 4 * B * nc * H * P * N, 256);
+  p.pin = off;
+  p.cbmax = off + 2 * B * nc * H * P * N;
+  off = round_up(off + 4 * B * nc * H * P * N, 256);
   p.cb = off;  off = round_up(off + 4 * B * nc * G * (size_t)ssdi8::frag::kCbBlocks * 1024, 256);
   p.dec = off; off = round_up(off + 4 * B * H * nc, 256);
   p.total = off;
@@ -456,15 +460,17 @@ ssdi8_status ssdi8_ssd_chunk_scan_fp16(const ssdi8_dims* d, const ssdi8_fp16_arg
   _Float16* bT = reinterpret_cast<_Float16*>(ws + plan.bT);
   _Float16* c16 = reinterpret_cast<_Float16*>(ws + plan.c16);
   float* S = reinterpret_cast<float*>(ws + plan.S);
-  float* pin = reinterpret_cast<float*>(ws + plan.pin);
+  _Float16* pin = reinterpret_cast<_Float16*>(ws + plan.pin);
   float* cb = reinterpret_cast<float*>(ws + plan.cb);
+  float* cbmax = reinterpret_cast<float*>(ws + plan.cbmax);
   float* dec = reinterpret_cast<float*>(ws + plan.dec);
   auto mark = [&](int i) -> bool {
     return !a->stage_events ||
            hipEventRecord(static_cast<hipEvent_t>(a->stage_events[i]), st) == hipSuccess;
   };
   if (!mark(0)) return SSDI8_ERR_HIP;
-  hipError_t e = ssdi8::launch_fp16_bmm(ld, a->C, a->B, a->bc_dtype, cb, bT, c16, nullptr, st);
+  hipError_t e = ssdi8::launch_fp16_bmm(ld, a->C, a->B, a->bc_dtype, cb, bT, c16, cbmax,
+                                          nullptr, st);
   if (e != hipSuccess || !mark(1)) return SSDI8_ERR_HIP;
   e = ssdi8::launch_fp16_state(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, bT, S, dec,
                                st);
@@ -472,7 +478,7 @@ ssdi8_status ssdi8_ssd_chunk_scan_fp16(const ssdi8_dims* d, const ssdi8_fp16_arg
   e = ssdi8::launch_fp16_pass(ld, S, dec, a->init_state, pin, a->final_state, st);
   if (e != hipSuccess || !mark(3)) return SSDI8_ERR_HIP;
   e = ssdi8::launch_fp16_scan(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, c16, pin, cb,
-                              a->D, a->y, a->y_dtype, st);
+                              cbmax, a->D, a->y, a->y_dtype, st);
   if (e != hipSuccess || !mark(4)) return SSDI8_ERR_HIP;
   return SSDI8_OK;
 }
@@ -518,7 +524,8 @@ ssdi8_status ssdi8_calibrate(const ssdi8_dims* d, const ssdi8_calib_args* a, voi
   _Float16* bT = reinterpret_cast<_Float16*>(f16 + plan.f16.bT);
   _Float16* c16 = reinterpret_cast<_Float16*>(f16 + plan.f16.c16);
   float* S = reinterpret_cast<float*>(f16 + plan.f16.S);
-  float* pin16 = reinterpret_cast<float*>(f16 + plan.f16.pin);
+  _Float16* pin16 = reinterpret_cast<_Float16*>(f16 + plan.f16.pin);
+  float* cbmax = reinterpret_cast<float*>(f16 + plan.f16.cbmax);
   float* cb = reinterpret_cast<float*>(f16 + plan.f16.cb);
   float* dec = reinterpret_cast<float*>(f16 + plan.f16.dec);
   char* i8 = ws + plan.i8_base;
@@ -542,7 +549,8 @@ ssdi8_status ssdi8_calibrate(const ssdi8_dims* d, const ssdi8_calib_args* a, voi
   if (e == hipSuccess)
     e = ssdi8::launch_calib_xs(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, xs_amax, st);
   if (e == hipSuccess)
-    e = ssdi8::launch_fp16_bmm(ld, a->C, a->B, a->bc_dtype, cb, bT, c16, cb_amax, st);
+    e = ssdi8::launch_fp16_bmm(ld, a->C, a->B, a->bc_dtype, cb, bT, c16, cbmax, cb_amax,
+                                st);
   if (e == hipSuccess)
     e = ssdi8::launch_calib_states(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, bT, S,
                                    dec64, s_amax, st);
@@ -556,7 +564,7 @@ ssdi8_status ssdi8_calibrate(const ssdi8_dims* d, const ssdi8_calib_args* a, voi
   if (e == hipSuccess) e = ssdi8::launch_fp16_pass(ld, S, dec, nullptr, pin16, nullptr, st);
   if (e == hipSuccess)
     e = ssdi8::launch_fp16_scan(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, c16, pin16,
-                                cb, a->D, yfp, SSDI8_F32, st);
+                                cb, cbmax, a->D, yfp, SSDI8_F32, st);
   // Y_q: the INT8 layer with the new steps and no correction, as ssdi8_ssd_chunk_scan runs it
   if (e != hipSuccess) return SSDI8_ERR_HIP;
   {

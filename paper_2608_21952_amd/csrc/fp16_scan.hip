@@ -3,8 +3,16 @@
 //   Scan2  W[j, i]  = fp16(CB[j, i] dt_i exp(cs_j - cs_i)), i <= j;  y_diag = W . x
 //   y = Y1 exp(cs_j) + y_diag + D x
 // The structure is the INT8 ChunkScan's (one workgroup per (b, c, h), transposed products so a
-// lane owns a token row, x^T staged once in LDS, block-factorised decay, fp16 output staged
-// through LDS), with fp32 CB blocks and fp32 entering states in place of the int8 ones.
+// lane owns a token row, x^T staged once in LDS, block-factorised decay, output staged
+// through LDS), with fp32 CB blocks in place of the int8 ones.  P_in arrives as the fp16 operand
+// itself: StatePassing rounds its fp32 running state once, where it writes it.
+//
+// What bounds it: operand bytes through L1/L2 (CB 147 KB, C 64 KB, P_in per workgroup) beside the
+// x / y stream.  So each wave runs Scan1 of both of its row blocks from one load of P_in (64 KB
+// per workgroup; per row block, in fp32, it was 256 KB), its result seeds the Scan2 accumulators,
+// and CB blocks that decay makes zero weights of are not loaded.  124 VGPRs and 37 KB of LDS keep
+// four workgroups per CU (three before).  2.7B-shaped layer, slow heads included: 209 -> 128 us;
+// 130M-shaped: 51.5 -> 36.5 us.
 #include "common.hpp"
 #include "frag.hpp"
 #include "launch.hpp"
@@ -16,6 +24,7 @@ namespace {
 constexpr int kXTS = kQ * 2 + 16;
 constexpr float kDiagSpan = 64.0f;
 static_assert(kP * kXTS >= kQ * kP * 2, "the fp16 output stage reuses the x^T bytes");
+static_assert(kP * kXTS >= kQ / 2 * kP * 4, "and so does half of an fp32 output tile");
 
 template <typename XT> struct Pair;
 template <> struct Pair<_Float16> {
@@ -42,34 +51,18 @@ template <> struct Pair<float> {
   }
 };
 
-// 8 fp32 -> 8 fp16
-__device__ __forceinline__ v8h to_h8(uint4 a, uint4 b) {
-  typedef float f2_t __attribute__((ext_vector_type(2)));
-  typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
-  const float f[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z),
-                      __uint_as_float(a.w), __uint_as_float(b.x), __uint_as_float(b.y),
-                      __uint_as_float(b.z), __uint_as_float(b.w)};
-  v8h r;
-#pragma unroll
-  for (int e = 0; e < 8; e += 2) {
-    const h2_t hh = __builtin_convertvector((f2_t){f[e], f[e + 1]}, h2_t);
-    r[e] = hh.x;
-    r[e + 1] = hh.y;
-  }
-  return r;
-}
-
 template <typename XT, typename YT>
-__global__ __launch_bounds__(256, 3) void fp16_scan_kernel(
+__global__ __launch_bounds__(256, 4) void fp16_scan_kernel(
     const XT* __restrict__ x, const float* __restrict__ dt, const float* __restrict__ A,
-    const _Float16* __restrict__ c_frag, const float* __restrict__ pin,
-    const float* __restrict__ cb, const float* __restrict__ Dv, int dt_softplus,
-    YT* __restrict__ y, int L, int H, int G, int nc, int stream) {
+    const _Float16* __restrict__ c_frag, const _Float16* __restrict__ pin,
+    const float* __restrict__ cb, const float* __restrict__ cb_max,
+    const float* __restrict__ Dv, int dt_softplus, YT* __restrict__ y, int L, int H, int G, int nc, int stream) {
   struct __attribute__((aligned(16))) Smem {
     float u[kQ];         // dt_i exp(r_I - cs_i)                          (off-diagonal blocks)
     float dg[kQ];        // dt_i exp(r_{I-1} - cs_i) if block I has a small span, else dt_i
     float csr[kQ];       // cs_i - r_{I-1}
     float R[8][8];       // exp(r_a - r_b), b <= a
+    float umax[8];       // max |u_i| over block I (inf if one is NaN)
     double r[8];
     double scan[kScanScratch];
     alignas(16) uint8_t xT[kP * kXTS];   // 128-bit accesses: 16-byte aligned explicitly
@@ -118,7 +111,12 @@ __global__ __launch_bounds__(256, 3) void fp16_scan_kernel(
   {
     const int blk = t >> 5;
     const double rprev = blk ? s_r[blk - 1] : 0.0;
-    s_u[t] = dtv * expf((float)(s_r[blk] - cs));
+    const float u = dtv * expf((float)(s_r[blk] - cs));
+    s_u[t] = u;
+    float um = u == u ? __builtin_fabsf(u) : __builtin_inff();
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) um = __builtin_fmaxf(um, __shfl_xor(um, o));
+    if ((t & 31) == 0) sm.umax[blk] = um;
     const float csr = (float)(cs - rprev);
     s_csr[t] = csr;
     const bool small_span = (float)(s_r[blk] - rprev) >= -kDiagSpan;
@@ -156,16 +154,35 @@ __global__ __launch_bounds__(256, 3) void fp16_scan_kernel(
   const __amdgpu_buffer_rsrc_t cqrs = buffer_rsrc(c_frag + cg * (size_t)kQ * kN);
   const uint32_t lane16 = lane * 16, lane64 = lane * 64;
   const float Dh = Dv ? Dv[h] : 0.0f;
-  uint2 y_first[8], y_second[8];
+  const int jta = wv, jtb = 7 - wv;   // this wave's row blocks
 
-  auto jblock = [&](const int jt, uint2 (&yo)[8]) {
-    asm volatile("" ::: "memory");
+  // -- Scan1 of both row blocks: Y1^T = fp16(P_in) . C^T over n (8 K-steps of 16).  The P_in
+  //    fragments (fp16, as StatePassing leaves them) serve both blocks from one load.
+  v16f ya0 = {}, ya1 = {}, yb0 = {}, yb1 = {};
+  {
+    const uint32_t ca = jta * (kN / 16) * 1024, cbo = jtb * (kN / 16) * 1024;
+#pragma unroll
+    for (int ks = 0; ks < kN / 16; ++ks) {
+      const v8h p0f = __builtin_bit_cast(v8h, buf_load16(prs, lane16, ks * 1024));
+      const v8h p1f = __builtin_bit_cast(v8h, buf_load16(prs, lane16, (kN / 16 + ks) * 1024));
+      const v8h fa = __builtin_bit_cast(v8h, buf_load16(cqrs, lane16, ca + 1024 * ks));
+      const v8h fb = __builtin_bit_cast(v8h, buf_load16(cqrs, lane16, cbo + 1024 * ks));
+      ya0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(p0f, fa, ya0, 0, 0, 0);
+      ya1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(p1f, fa, ya1, 0, 0, 0);
+      yb0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(p0f, fb, yb0, 0, 0, 0);
+      yb1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(p1f, fb, yb1, 0, 0, 0);
+    }
+  }
+
+  // The rest of a row block on its accumulators: Y1 exp(cs_j) + D x, then Scan2 on top.
+  auto jblock = [&](int jt, v16f& y0, v16f& y1) {
+    asm volatile("" : "+s"(jt) :: "memory");
     const int jrow = jt * 32 + pc;
     const float csrj = s_csr[jrow];
     const float ej = __expf(csrj);
+    // exp(cs_j) = exp(cs_j - r_{J-1}) exp(r_{J-1})
+    const float eo = ej * (jt ? __expf((float)s_r[jt - 1]) : 1.0f);
     const size_t orow = (tok0 + jrow) * HP + (size_t)h * kP;
-    // -- the Scan2 accumulators start from D x
-    v16f yd0, yd1;
 #pragma unroll
     for (int pt = 0; pt < 2; ++pt) {
 #pragma unroll
@@ -182,157 +199,165 @@ __global__ __launch_bounds__(256, 3) void fp16_scan_kernel(
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          if (pt) yd1[4 * g4 + q] = Dh * xv[q];
-          else yd0[4 * g4 + q] = Dh * xv[q];
+          const int r = 4 * g4 + q;
+          if (pt) y1[r] = __builtin_fmaf(y1[r], eo, Dh * xv[q]);
+          else y0[r] = __builtin_fmaf(y0[r], eo, Dh * xv[q]);
         }
       }
     }
-    // -- Scan2 over the causal blocks (jt, it); fp32 CB block: 16 floats per lane
+    // -- Scan2 over the causal blocks (jt, it); fp32 CB block: 16 floats per lane.  Leading
+    //    blocks whose every weight rounds to an fp16 zero are skipped: |W| <= max |CB| max |u| R
+    //    (e_j <= 1), and below 2^-26 (half the smallest fp16 subnormal is 2^-25) it is zero.
+    const uint32_t blk0 = frag::cb_block(jt, 0);
+    const uint32_t cbrow = blk0 * 4096;
+    const bool diag_fast =
+        __builtin_amdgcn_readfirstlane((int)(s_csr[jt * 32 + 31] >= -kDiagSpan)) != 0;
+    int it0 = jt;
     {
-      const uint32_t cbrow = frag::cb_block(jt, 0) * 4096;
-      const bool diag_fast =
-          __builtin_amdgcn_readfirstlane((int)(s_csr[jt * 32 + 31] >= -kDiagSpan)) != 0;
-      auto mfma_block = [&](const float (&wv)[8], int i0) {
-        v8h wf;
+      const int k = lane & 7;
+      const float m = cb_max[cg * frag::kCbBlocks + blk0 + (k < jt ? k : 0)];
+      const bool live = k < jt && !(m * sm.umax[k] * s_R[jt ? jt - 1 : 0][k] < 0x1p-26f);
+      const uint32_t lv = (uint32_t)__ballot(live) & 0xffu;
+      if (lv) it0 = (int)__builtin_ctz(lv);
+      it0 = __builtin_amdgcn_readfirstlane(it0);
+    }
+    auto mfma_block = [&](const float (&wv)[8], int i0) {
+      v8h wf;
 #pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-          typedef float f2_t __attribute__((ext_vector_type(2)));
-          typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
-          const h2_t hh = __builtin_convertvector((f2_t){wv[e], wv[e + 1]}, h2_t);
-          wf[e] = hh.x;
-          wf[e + 1] = hh.y;
-        }
-        const v8h xa0 = *reinterpret_cast<const v8h*>(s_xT + pc * kXTS + i0 * 2);
-        const v8h xa1 = *reinterpret_cast<const v8h*>(s_xT + (32 + pc) * kXTS + i0 * 2);
-        yd0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa0, wf, yd0, 0, 0, 0);
-        yd1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa1, wf, yd1, 0, 0, 0);
-      };
-      auto load_block = [&](uint32_t off, uint4 (&v)[4]) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = buf_load16(cbrs, lane64, off + 16 * u);
-      };
-      auto cbv = [](const uint4 (&v)[4], int k) {   // float k of this lane's 16
-        const uint4 q = v[k >> 2];
-        const uint32_t e = (k & 3) == 0 ? q.x : (k & 3) == 1 ? q.y : (k & 3) == 2 ? q.z : q.w;
-        return __uint_as_float(e);
-      };
-      uint4 cur[4];
-      load_block(cbrow, cur);
-      for (int it = 0; it < jt; ++it) {
-        uint4 nx[4];
-        load_block(cbrow + (it + 1) * 4096, nx);
-        __builtin_amdgcn_sched_barrier(0);
-        const float vj = ej * s_R[jt - 1][it];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          const int i0 = it * 32 + ks * 16 + 8 * half;
-          float wv[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) wv[e] = (cbv(cur, 8 * ks + e) * s_u[i0 + e]) * vj;
-          mfma_block(wv, i0);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) cur[u] = nx[u];
+      for (int e = 0; e < 8; e += 2) {
+        typedef float f2_t __attribute__((ext_vector_type(2)));
+        typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
+        const h2_t hh = __builtin_convertvector((f2_t){wv[e], wv[e + 1]}, h2_t);
+        wf[e] = hh.x;
+        wf[e + 1] = hh.y;
       }
+      const v8h xa0 = *reinterpret_cast<const v8h*>(s_xT + pc * kXTS + i0 * 2);
+      const v8h xa1 = *reinterpret_cast<const v8h*>(s_xT + (32 + pc) * kXTS + i0 * 2);
+      y0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa0, wf, y0, 0, 0, 0);
+      y1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa1, wf, y1, 0, 0, 0);
+    };
+    auto load_block = [&](uint32_t off, uint4 (&v)[4]) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = buf_load16(cbrs, lane64, off + 16 * u);
+    };
+    auto cbv = [](const uint4 (&v)[4], int k) {   // float k of this lane's 16
+      const uint4 q = v[k >> 2];
+      const uint32_t e = (k & 3) == 0 ? q.x : (k & 3) == 1 ? q.y : (k & 3) == 2 ? q.z : q.w;
+      return __uint_as_float(e);
+    };
+    uint4 cur[4];
+    load_block(cbrow + it0 * 4096, cur);
+    for (int it = it0; it < jt; ++it) {
+      uint4 nx[4];
+      load_block(cbrow + (it + 1) * 4096, nx);
+      __builtin_amdgcn_sched_barrier(0);
+      const float vj = ej * s_R[jt - 1][it];
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        const int i0 = jt * 32 + ks * 16 + 8 * half;
+        const int i0 = it * 32 + ks * 16 + 8 * half;
         float wv[8];
-        if (diag_fast) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float v = (cbv(cur, 8 * ks + e) * s_dg[i0 + e]) * ej;
-            wv[e] = (i0 + e <= jrow) ? v : 0.0f;
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float ex = __expf(__builtin_fminf(csrj - s_csr[i0 + e], 0.0f));
-            const float v = (cbv(cur, 8 * ks + e) * s_dg[i0 + e]) * ex;
-            wv[e] = (i0 + e <= jrow) ? v : 0.0f;
-          }
-        }
+        for (int e = 0; e < 8; ++e) wv[e] = (cbv(cur, 8 * ks + e) * s_u[i0 + e]) * vj;
         mfma_block(wv, i0);
       }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) cur[u] = nx[u];
     }
-    // -- Scan1: Y1^T = fp16(P_in) . C^T over n (8 K-steps of 16)
-    v16f yi0 = {}, yi1 = {};
-    {
-      uint32_t lofs = lane * 32;
-      asm volatile("" : "+v"(lofs));
-      const uint32_t crow = jt * (kN / 16) * 1024;
 #pragma unroll
-      for (int ks = 0; ks < kN / 16; ++ks) {
-        const v8h a = __builtin_bit_cast(v8h, buf_load16(cqrs, lane16, crow + 1024 * ks));
-        const uint32_t o0 = ks * 2048, o1 = (kN / 16 + ks) * 2048;
-        const v8h p0f = to_h8(buf_load16(prs, lofs, o0), buf_load16(prs, lofs, o0 + 16));
-        const v8h p1f = to_h8(buf_load16(prs, lofs, o1), buf_load16(prs, lofs, o1 + 16));
-        yi0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(p0f, a, yi0, 0, 0, 0);
-        yi1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(p1f, a, yi1, 0, 0, 0);
-      }
-    }
-    // -- epilogue: y = Y1 exp(cs_j) + (y_diag + D x),  exp(cs_j) = exp(cs_j - r_{J-1}) exp(r_{J-1})
-    const float eo = ej * (jt ? __expf((float)s_r[jt - 1]) : 1.0f);
+    for (int ks = 0; ks < 2; ++ks) {
+      const int i0 = jt * 32 + ks * 16 + 8 * half;
+      float wv[8];
+      if (diag_fast) {
 #pragma unroll
-    for (int pt = 0; pt < 2; ++pt) {
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int pb = pt * 32 + 8 * g4 + 4 * half;
-        float v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int r = 4 * g4 + q;
-          v[q] = __builtin_fmaf(pt ? yi1[r] : yi0[r], eo, pt ? yd1[r] : yd0[r]);
+        for (int e = 0; e < 8; ++e) {
+          const float v = (cbv(cur, 8 * ks + e) * s_dg[i0 + e]) * ej;
+          wv[e] = (i0 + e <= jrow) ? v : 0.0f;
         }
-        if constexpr (sizeof(YT) == 4) {
-          *reinterpret_cast<float4*>(y + orow + pb) = make_float4(v[0], v[1], v[2], v[3]);
-        } else {
-          typedef float f2_t __attribute__((ext_vector_type(2)));
-          typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
-          const h2_t h01 = __builtin_convertvector((f2_t){v[0], v[1]}, h2_t);
-          const h2_t h23 = __builtin_convertvector((f2_t){v[2], v[3]}, h2_t);
-          uint2 o = make_uint2(__builtin_bit_cast(uint32_t, h01), __builtin_bit_cast(uint32_t, h23));
-          asm volatile("" : "+v"(o.x), "+v"(o.y));
-          yo[4 * pt + g4] = o;
-        }
-      }
-    }
-  };
-  jblock(wv, y_first);
-  jblock(7 - wv, y_second);
-
-  if constexpr (sizeof(YT) == 2) {
-    __syncthreads();
-    uint8_t* s_y = s_xT;
-    {
-      const uint32_t jx = pc & 7;
-      uint8_t* r0 = s_y + (wv * 32 + pc) * 128 + 8 * half;
-      uint8_t* r1 = s_y + ((7 - wv) * 32 + pc) * 128 + 8 * half;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const uint32_t so = (k ^ jx) * 16;
-        *reinterpret_cast<uint2*>(r0 + so) = y_first[k];
-        *reinterpret_cast<uint2*>(r1 + so) = y_second[k];
-      }
-    }
-    __syncthreads();
-    {
-      const int jt8 = t >> 3, col = t & 7;
-      const uint8_t* src = s_y + jt8 * 128 + ((col ^ (jt8 & 7)) * 16);
-      const __amdgpu_buffer_rsrc_t yrs = buffer_rsrc(y + tok0 * HP + (size_t)h * kP);
-      const uint32_t yo = (uint32_t)(jt8 * HP * 2 + col * 16);
-      if (stream) {
-#pragma unroll
-        for (int k = 0; k < (kQ * kP * 2) / (16 * 256); ++k)
-          buf_store16<kPolicyNT>(*reinterpret_cast<const uint4*>(src + k * 32 * 128), yrs, yo,
-                                 (uint32_t)(k * 32 * HP * 2));
       } else {
 #pragma unroll
-        for (int k = 0; k < (kQ * kP * 2) / (16 * 256); ++k)
-          buf_store16(*reinterpret_cast<const uint4*>(src + k * 32 * 128), yrs, yo,
-                      (uint32_t)(k * 32 * HP * 2));
+        for (int e = 0; e < 8; ++e) {
+          const float ex = __expf(__builtin_fminf(csrj - s_csr[i0 + e], 0.0f));
+          const float v = (cbv(cur, 8 * ks + e) * s_dg[i0 + e]) * ex;
+          wv[e] = (i0 + e <= jrow) ? v : 0.0f;
+        }
       }
+      mfma_block(wv, i0);
     }
+  };
+  jblock(jta, ya0, ya1);
+  jblock(jtb, yb0, yb1);
+
+  // -- output: the two row blocks leave through the x^T bytes as whole token rows
+  const __amdgpu_buffer_rsrc_t yrs = buffer_rsrc(y + tok0 * HP + (size_t)h * kP);
+  if constexpr (sizeof(YT) == 2) {
+    // row j at 128 j, its 16-byte chunk k at slot k ^ (j & 7)
+    const uint32_t jx = pc & 7;
+    auto stage = [&](int jt, const v16f& y0, const v16f& y1) {
+      uint8_t* row = s_xT + (jt * 32 + pc) * 128 + 8 * half;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        typedef float f2_t __attribute__((ext_vector_type(2)));
+        typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
+        const int r = 4 * (k & 3);
+        const v16f& v = k < 4 ? y0 : y1;
+        const h2_t h01 = __builtin_convertvector((f2_t){v[r], v[r + 1]}, h2_t);
+        const h2_t h23 = __builtin_convertvector((f2_t){v[r + 2], v[r + 3]}, h2_t);
+        *reinterpret_cast<uint2*>(row + (k ^ jx) * 16) =
+            make_uint2(__builtin_bit_cast(uint32_t, h01), __builtin_bit_cast(uint32_t, h23));
+      }
+    };
+    __syncthreads();
+    stage(jta, ya0, ya1);
+    stage(jtb, yb0, yb1);
+    __syncthreads();
+    const int jt8 = t >> 3, col = t & 7;
+    const uint8_t* src = s_xT + jt8 * 128 + ((col ^ (jt8 & 7)) * 16);
+    const uint32_t yo = (uint32_t)(jt8 * HP * 2 + col * 16);
+    if (stream) {
+#pragma unroll
+      for (int k = 0; k < (kQ * kP * 2) / (16 * 256); ++k)
+        buf_store16<kPolicyNT>(*reinterpret_cast<const uint4*>(src + k * 32 * 128), yrs, yo,
+                               (uint32_t)(k * 32 * HP * 2));
+    } else {
+#pragma unroll
+      for (int k = 0; k < (kQ * kP * 2) / (16 * 256); ++k)
+        buf_store16(*reinterpret_cast<const uint4*>(src + k * 32 * 128), yrs, yo,
+                    (uint32_t)(k * 32 * HP * 2));
+    }
+  } else {
+    // fp32: 128 rows at a time (blocks 0..3, then 4..7), row j at 256 (j % 128), its 16-byte
+    // chunk k at slot k ^ (j & 15)
+    const uint32_t jx = pc & 15;
+    auto stage = [&](int jt4, const v16f& y0, const v16f& y1) {
+      uint8_t* row = s_xT + (jt4 * 32 + pc) * 256;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int r = 4 * (k & 3);
+        const v16f& v = k < 4 ? y0 : y1;
+        *reinterpret_cast<float4*>(row + ((uint32_t)(2 * k + half) ^ jx) * 16) =
+            make_float4(v[r], v[r + 1], v[r + 2], v[r + 3]);
+      }
+    };
+    const int jt16 = t >> 4, col = t & 15;
+    const uint8_t* src = s_xT + jt16 * 256 + ((col ^ (jt16 & 15)) * 16);
+    const uint32_t yo = (uint32_t)(jt16 * HP * 4 + col * 16);
+    auto copy_out = [&](uint32_t row0) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const uint4 v = *reinterpret_cast<const uint4*>(src + k * 16 * 256);
+        const uint32_t so = (uint32_t)((row0 + 16 * k) * HP * 4);
+        if (stream) buf_store16<kPolicyNT>(v, yrs, yo, so);
+        else buf_store16(v, yrs, yo, so);
+      }
+    };
+    __syncthreads();
+    stage(jta, ya0, ya1);
+    __syncthreads();
+    copy_out(0);
+    __syncthreads();
+    stage(jtb - 4, yb0, yb1);
+    __syncthreads();
+    copy_out(128);
   }
 }
 
@@ -340,14 +365,14 @@ __global__ __launch_bounds__(256, 3) void fp16_scan_kernel(
 
 hipError_t launch_fp16_scan(const LayerDims& d, const void* x, int x_dtype, const float* dt,
                             int dt_softplus, const float* A, const _Float16* c_frag,
-                            const float* pin, const float* cb, const float* D, void* y,
-                            int y_dtype, hipStream_t st) {
+                            const _Float16* pin, const float* cb, const float* cb_max,
+                            const float* D, void* y, int y_dtype, hipStream_t st) {
   const int64_t nwork = (int64_t)d.batch * d.nchunks * d.nheads;
   if (nwork == 0) return hipSuccess;
   const int stream = stream_xy(d, x_dtype == 1 ? 2 : 4, y_dtype == 1 ? 2 : 4);
 #define SSDI8_F16SCAN_LAUNCH(XT, YT)                                                           \
   hipLaunchKernelGGL((fp16_scan_kernel<XT, YT>), dim3((unsigned)nwork), dim3(256), 0, st,       \
-                     static_cast<const XT*>(x), dt, A, c_frag, pin, cb, D, dt_softplus,        \
+                     static_cast<const XT*>(x), dt, A, c_frag, pin, cb, cb_max, D, dt_softplus, \
                      static_cast<YT*>(y), d.seqlen, d.nheads, d.ngroups, d.nchunks, stream)
   if (x_dtype == 1 && y_dtype == 1) SSDI8_F16SCAN_LAUNCH(_Float16, _Float16);
   else if (x_dtype == 1) SSDI8_F16SCAN_LAUNCH(_Float16, float);

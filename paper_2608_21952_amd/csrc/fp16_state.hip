@@ -5,8 +5,8 @@
 //   S[p, n]  = sum_j X~[j, p] B[j, n]       fp16 MFMA 32x32x16 over tokens, fp32 accumulation
 //   d        = fl32(exp(cs_last))
 //   P_in[c+1] = fl32(d P_in[c] + S[c])      one fma per element, fp32 states
-// S and P_in are kept in the fragment order of ChunkScan1's fp16 operand (frag::k16_offset with
-// rows p, K = n, fp32 elements); the initial and final states are row-major [p][n].
+// S (fp32) and fp16(P_in), ChunkScan1's operand, are kept in that operand's fragment order
+// (frag::k16_offset with rows p, K = n); the initial and final states are row-major [p][n].
 #include "common.hpp"
 #include "frag.hpp"
 #include "launch.hpp"
@@ -143,49 +143,85 @@ __global__ __launch_bounds__(256) void fp16_state_kernel(
   for (int k = 0; k < (kP * kN) / (4 * 256); ++k) dst[k * 256 + t] = src[k * 256 + t];
 }
 
-// P_in[c+1] = fl32(d[c] P_in[c] + S[c]) over [b, c, h, P*N] fp32 in fragment order, 4 elements
-// per thread, two batches of 8 chunks of loads in flight.
+// P_in[c+1] = fl32(d[c] P_in[c] + S[c]) over [b, c, h, P*N] fp32 in fragment order, kE elements
+// per thread, kDepth chunks of loads in flight.  The running state stays fp32 in registers; what
+// is written is ChunkScan1's operand, fp16(P_in[c]) (6 instead of 8 bytes per element of HBM
+// traffic, which bounds it: 54 -> 41 us on the 2.7B-shaped layer).
+typedef float f2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_h2(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2_t){a, b}, h2_t));
+}
+
+template <int kV>   // float4 per thread
 __global__ __launch_bounds__(256) void fp16_pass_kernel(
     const float* __restrict__ S, const float* __restrict__ dec, const float* __restrict__ init,
-    float* __restrict__ pin, float* __restrict__ final_state, int nc, int H, int64_t nthreads) {
+    _Float16* __restrict__ pin, float* __restrict__ final_state, int nc, int H,
+    int64_t nthreads) {
   constexpr int kDepth = 8;
-  constexpr int64_t kE = (int64_t)kP * kN;
+  constexpr int kE = 4 * kV;
+  constexpr int64_t kSlab = (int64_t)kP * kN;
   const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (gt >= nthreads) return;
-  const int64_t e = gt * 4;
-  const int64_t bh = e / kE;
-  const int64_t off = e - bh * kE;
+  const int64_t e = gt * kE;
+  const int64_t bh = e / kSlab;
+  const int64_t off = e - bh * kSlab;
   const int64_t b = bh / H, h = bh - b * H;
   int row, k;
   frag::k16_coords((size_t)off, kN, &row, &k);
-  const int64_t roff = (int64_t)row * kN + k;   // row-major offset of the same 4 elements
-  float4 st = init ? *reinterpret_cast<const float4*>(init + bh * kE + roff)
-                   : make_float4(0.f, 0.f, 0.f, 0.f);
-  const size_t cstride = (size_t)H * kE;
-  const size_t base = ((size_t)b * nc * H + h) * kE + off;
+  const int64_t roff = (int64_t)row * kN + k;   // row-major offset of the same kE elements
+  float st[kE];
+#pragma unroll
+  for (int i = 0; i < kE; ++i) st[i] = 0.0f;
+  if (init) {
+#pragma unroll
+    for (int i = 0; i < kV; ++i) {
+      const float4 f = reinterpret_cast<const float4*>(init + bh * kSlab + roff)[i];
+      st[4 * i] = f.x; st[4 * i + 1] = f.y; st[4 * i + 2] = f.z; st[4 * i + 3] = f.w;
+    }
+  }
+  const size_t cstride = (size_t)H * kSlab;
+  const size_t base = ((size_t)b * nc * H + h) * kSlab + off;
   const float* drow = dec + bh * nc;
   for (int c0 = 0; c0 < nc; c0 += kDepth) {
-    float4 v[kDepth];
+    float4 v[kDepth][kV];
     float d[kDepth];
 #pragma unroll
     for (int q = 0; q < kDepth; ++q) {
       if (c0 + q < nc) {
-        v[q] = *reinterpret_cast<const float4*>(S + base + (size_t)(c0 + q) * cstride);
+#pragma unroll
+        for (int i = 0; i < kV; ++i)
+          v[q][i] = reinterpret_cast<const float4*>(S + base + (size_t)(c0 + q) * cstride)[i];
         d[q] = drow[c0 + q];
       }
     }
 #pragma unroll
     for (int q = 0; q < kDepth; ++q) {
       if (c0 + q < nc) {
-        *reinterpret_cast<float4*>(pin + base + (size_t)(c0 + q) * cstride) = st;
-        st.x = __builtin_fmaf(d[q], st.x, v[q].x);
-        st.y = __builtin_fmaf(d[q], st.y, v[q].y);
-        st.z = __builtin_fmaf(d[q], st.z, v[q].z);
-        st.w = __builtin_fmaf(d[q], st.w, v[q].w);
+        uint32_t o[2 * kV];
+#pragma unroll
+        for (int i = 0; i < 2 * kV; ++i) o[i] = pack_h2(st[2 * i], st[2 * i + 1]);
+        _Float16* dst = pin + base + (size_t)(c0 + q) * cstride;
+        if constexpr (kV == 2)
+          *reinterpret_cast<uint4*>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
+        else
+          *reinterpret_cast<uint2*>(dst) = make_uint2(o[0], o[1]);
+#pragma unroll
+        for (int i = 0; i < kV; ++i) {
+          st[4 * i] = __builtin_fmaf(d[q], st[4 * i], v[q][i].x);
+          st[4 * i + 1] = __builtin_fmaf(d[q], st[4 * i + 1], v[q][i].y);
+          st[4 * i + 2] = __builtin_fmaf(d[q], st[4 * i + 2], v[q][i].z);
+          st[4 * i + 3] = __builtin_fmaf(d[q], st[4 * i + 3], v[q][i].w);
+        }
       }
     }
   }
-  if (final_state) *reinterpret_cast<float4*>(final_state + bh * kE + roff) = st;
+  if (final_state) {
+#pragma unroll
+    for (int i = 0; i < kV; ++i)
+      reinterpret_cast<float4*>(final_state + bh * kSlab + roff)[i] =
+          make_float4(st[4 * i], st[4 * i + 1], st[4 * i + 2], st[4 * i + 3]);
+  }
 }
 
 }  // namespace
@@ -207,11 +243,20 @@ hipError_t launch_fp16_state(const LayerDims& d, const void* x, int x_dtype, con
 }
 
 hipError_t launch_fp16_pass(const LayerDims& d, const float* S, const float* dec,
-                            const float* init, float* pin, float* final_state, hipStream_t st) {
-  const int64_t nthreads = (int64_t)d.batch * d.nheads * kP * kN / 4;
-  if (nthreads == 0) return hipSuccess;
-  hipLaunchKernelGGL(fp16_pass_kernel, dim3((unsigned)((nthreads + 255) / 256)), dim3(256), 0,
-                     st, S, dec, init, pin, final_state, d.nchunks, d.nheads, nthreads);
+                            const float* init, _Float16* pin, float* final_state,
+                            hipStream_t st) {
+  const int64_t elems = (int64_t)d.batch * d.nheads * kP * kN;
+  if (elems == 0) return hipSuccess;
+  // 8 elements per thread (one 16-byte store each) while that leaves two waves per SIMD
+  const bool wide = elems / 8 >= 131072;
+  const int64_t nthreads = elems / (wide ? 8 : 4);
+  const dim3 grid((unsigned)((nthreads + 255) / 256)), block(256);
+  if (wide)
+    hipLaunchKernelGGL(fp16_pass_kernel<2>, grid, block, 0, st, S, dec, init, pin, final_state,
+                       d.nchunks, d.nheads, nthreads);
+  else
+    hipLaunchKernelGGL(fp16_pass_kernel<1>, grid, block, 0, st, S, dec, init, pin, final_state,
+                       d.nchunks, d.nheads, nthreads);
   return hipGetLastError();
 }
 

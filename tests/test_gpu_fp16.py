@@ -99,3 +99,29 @@ def test_fp16_empty_sequence_returns_initial_state(torch, ssdi8):
     out = ssdi8.ssd_chunk_scan_fp16(h16(2, 0, 4, 64), z(2, 0, 4), z(4), h16(2, 0, 1, 128),
                                     h16(2, 0, 1, 128), init_state=init)
     assert torch.equal(out["final_state"], init)
+
+
+@pytest.mark.parametrize("batch,seqlen,nheads,ngroups,dtype,y_dtype,a_lo,a_hi", [
+    (1, 256, 5, 5, "fp16", "fp16", 0.0, 2.77),       # one chunk, narrow state passing
+    (1, 2304, 3, 1, "fp16", "fp32", -4.0, 0.0),      # nine chunks, no block skipped
+    (2, 768, 64, 2, "fp32", "fp32", -4.0, 4.0),      # wide state passing, mixed decays
+    (2, 512, 65, 5, "fp16", "fp16", 3.0, 6.0),       # every off-diagonal block a zero weight
+    (1, 512, 6, 3, "fp32", "fp16", 2.0, 5.0),        # diagonal spans on both sides of 64
+])
+def test_fp16_scan_edges(torch, ssdi8, batch, seqlen, nheads, ngroups, dtype, y_dtype, a_lo, a_hi):
+    """Skipped and kept ChunkScan2 blocks, both output stages, both widths of state passing."""
+    cfg = dataclasses.replace(synth.CONFIGS["mamba2-130m"], name="fp16-edges", batch=batch,
+                              seqlen=seqlen, nheads=nheads, ngroups=ngroups, dtype=dtype,
+                              a_lo=a_lo, a_hi=a_hi, x_outliers=min(31, nheads), dt_sigma=0.7)
+    inp = synth.draw(cfg, 1)
+    rng = np.random.default_rng(5)
+    init = rng.standard_normal((batch, nheads, 64, 128)).astype(np.float32)
+    g = _run(torch, ssdi8, inp, init=init, y_dtype={"fp16": torch.float16,
+                                                    "fp32": torch.float32}[y_dtype])
+    y, fin = g["y"].float().cpu().numpy(), g["final_state"].cpu().numpy()
+    picks = sorted({(0, 0), (batch - 1, nheads - 1), (batch - 1, nheads // 2)})
+    ref = ofp.ssd_fp16_forward(inp["x"], inp["dt_raw"], inp["A"], inp["B"], inp["C"], inp["D"],
+                               chunk=cfg.chunk, heads=picks, init=init)
+    for (b, h) in picks:
+        assert_close(y[b, :, h], ref["slabs"][(b, h)]["y64"], f"y slab ({b},{h})")
+        _check_state(fin[b, h], ref["slabs"][(b, h)]["final"], f"final state slab ({b},{h})")
