@@ -2,8 +2,9 @@
 //   CB[j, i] = sum_n C[j, n] B[i, n]   for i <= j   (fp16 MFMA 32x32x16, fp32 accumulation)
 // stored in fp32, as the 36 causal 32x32 blocks of each (b, c, g) in the fragment order in which
 // ChunkScan2 builds its weights (frag::cb_inblock, in fp32 elements).  Like the INT8 ChunkBMM it
-// also leaves the operands of the later kernels in fragment order (frag::k16_offset): C rows of
-// the chunk (ChunkScan1, K = n) and B^T of the chunk (ChunkState, rows n, K = tokens).
+// also leaves the operands of the later kernels in fragment order: C rows of the chunk
+// (ChunkScan1, K = n; frag::pk16_offset) and B^T of the chunk (ChunkState, rows n, K = tokens;
+// frag::k16_offset).
 // Work item = (b, c, g, role): roles 0..8 compute 4 causal tiles each (one per wave), role 9
 // transposes B.
 #include "common.hpp"
@@ -106,10 +107,17 @@ __global__ __launch_bounds__(256) void fp16_bmm_kernel(const T* __restrict__ C,
     // the C rows of block jt in ChunkScan1 fragment order (before the MFMA chain, so that no
     // branch separates the last MFMA from the reads of its result)
     _Float16* cdst = c_frag + cg * (size_t)kQ * kN;
+    // pk16 order: lane (j, h) holds n = 4 h + [0, 4) and 8 + 4 h + [0, 4); it has n = 8 h + [0,
+    // 8): the lower half-wave keeps its first 8 bytes and takes the upper half's, the upper half
+    // takes the lower half's last 8 bytes and keeps its own
 #pragma unroll
-    for (int ks = 0; ks < kN / 16; ++ks)
-      *reinterpret_cast<h8*>(cdst + frag::k16_offset(jt * 32 + (lane & 31), 16 * ks + 8 * half,
-                                                     kN)) = cf[ks];
+    for (int ks = 0; ks < kN / 16; ++ks) {
+      const uint4 v = __builtin_bit_cast(uint4, cf[ks]);
+      const auto s02 = __builtin_amdgcn_permlane32_swap(v.x, v.z, false, false);
+      const auto s13 = __builtin_amdgcn_permlane32_swap(v.y, v.w, false, false);
+      *reinterpret_cast<uint4*>(cdst + ((size_t)jt * (kN / 16) + ks) * 512 + lane * 8) =
+          make_uint4(s02[0], s13[0], s02[1], s13[1]);
+    }
   }
   v16f acc = {};
 #pragma unroll

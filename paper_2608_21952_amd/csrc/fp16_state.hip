@@ -5,8 +5,10 @@
 //   S[p, n]  = sum_j X~[j, p] B[j, n]       fp16 MFMA 32x32x16 over tokens, fp32 accumulation
 //   d        = fl32(exp(cs_last))
 //   P_in[c+1] = fl32(d P_in[c] + S[c])      one fma per element, fp32 states
-// S (fp32) and fp16(P_in), ChunkScan1's operand, are kept in that operand's fragment order
-// (frag::k16_offset with rows p, K = n); the initial and final states are row-major [p][n].
+// fp16(P_in), ChunkScan1's operand, is kept in that operand's fragment order (frag::pk16_offset
+// with rows p, K = n); S in the same order split into planes of four elements per lane (the order
+// in which the accumulators hold it, so that every store covers a contiguous 1 KB); the initial
+// and final states are row-major [p][n].
 #include "common.hpp"
 #include "frag.hpp"
 #include "launch.hpp"
@@ -108,39 +110,34 @@ __global__ __launch_bounds__(256) void fp16_state_kernel(
   }
   __syncthreads();
 
-  // ---- S = X~^T B: wave -> p-tile mt (32 rows), n-tiles ntb, ntb + 1
-  const int mt = wv & 1, ntb = (wv >> 1) * 2, half = lane >> 5;
-  const _Float16* bq = bT_frag + (((size_t)b * nc + c) * G + g) * (size_t)kN * kQ;
+  // ---- S^T = B^T X~ (rows n, columns p): wave -> n-tile wv and both p-tiles, so that each B^T
+  //      fragment (64 KB per chunk, from L2) is loaded by one wave.  The result leaves every
+  //      lane with the fp32 elements of its fragment slices, so S goes to memory straight from
+  //      the accumulators.
+  const int half = lane >> 5;
   v16f acc0 = {}, acc1 = {};
   {
-    const uint8_t* arow = s_x + (mt * 32 + (lane & 31)) * kXS + 16 * half;
-    const _Float16* b0f = bq + (size_t)ntb * (kQ / 16) * 512 + lane * 8;
-    const _Float16* b1f = b0f + (size_t)(kQ / 16) * 512;
+    const uint8_t* arow = s_x + (lane & 31) * kXS + 16 * half;
+    const _Float16* bf = bT_frag + (((size_t)b * nc + c) * G + g) * (size_t)kN * kQ +
+                         (size_t)wv * (kQ / 16) * 512 + lane * 8;
 #pragma unroll
     for (int ks = 0; ks < kQ / 16; ++ks) {
-      const h8 a = *reinterpret_cast<const h8*>(arow + ks * 32);
-      const h8 b0 = *reinterpret_cast<const h8*>(b0f + ks * 512);
-      const h8 b1 = *reinterpret_cast<const h8*>(b1f + ks * 512);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b0, acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b1, acc1, 0, 0, 0);
+      const h8 b0 = *reinterpret_cast<const h8*>(bf + ks * 512);
+      const h8 a0 = *reinterpret_cast<const h8*>(arow + ks * 32);
+      const h8 a1 = *reinterpret_cast<const h8*>(arow + 32 * kXS + ks * 32);
+      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(b0, a0, acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(b0, a1, acc1, 0, 0, 0);
     }
   }
-  __syncthreads();   // X~^T no longer read: its LDS stages S
-
-  // ---- stage S in ChunkScan1 fragment order (fp32), then 16-byte copies out
-  float* s_st = reinterpret_cast<float*>(s_x);
-  const int n0 = ntb * 32 + (lane & 31);
+  // run q (four rows n) of every lane of a tile is one 1 KB plane
+  float* dst = S + (((size_t)b * nc + c) * H + h) * (size_t)kP * kN + (size_t)wv * 1024 + lane * 4;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int p = mt * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-    s_st[frag::k16_offset(p, n0, kN)] = acc0[r];
-    s_st[frag::k16_offset(p, n0 + 32, kN)] = acc1[r];
+  for (int q = 0; q < 4; ++q) {
+    *reinterpret_cast<float4*>(dst + 256 * q) =
+        make_float4(acc0[4 * q], acc0[4 * q + 1], acc0[4 * q + 2], acc0[4 * q + 3]);
+    *reinterpret_cast<float4*>(dst + (kN / 32) * 1024 + 256 * q) =
+        make_float4(acc1[4 * q], acc1[4 * q + 1], acc1[4 * q + 2], acc1[4 * q + 3]);
   }
-  __syncthreads();
-  float4* dst = reinterpret_cast<float4*>(S + (((size_t)b * nc + c) * H + h) * (size_t)kP * kN);
-  const float4* src = reinterpret_cast<const float4*>(s_st);
-#pragma unroll
-  for (int k = 0; k < (kP * kN) / (4 * 256); ++k) dst[k * 256 + t] = src[k * 256 + t];
 }
 
 // P_in[c+1] = fl32(d[c] P_in[c] + S[c]) over [b, c, h, P*N] fp32 in fragment order, kE elements
@@ -165,23 +162,29 @@ __global__ __launch_bounds__(256) void fp16_pass_kernel(
   if (gt >= nthreads) return;
   const int64_t e = gt * kE;
   const int64_t bh = e / kSlab;
-  const int64_t off = e - bh * kSlab;
+  const int slot = (int)(e - bh * kSlab) / kE;   // lane slices (kV = 2) or their halves (kV = 1)
   const int64_t b = bh / H, h = bh - b * H;
+  // plane order of S: 256 floats per run of four k, 4 per lane; pin: 8 elements per lane slice
+  const int lane = slot & 63;
+  const int plane = (slot >> 6) * kV;
+  const int soff = plane * 256 + lane * 4;
+  const int off = (plane >> 1) * 512 + lane * 8 + 4 * (plane & 1);
   int row, k;
-  frag::k16_coords((size_t)off, kN, &row, &k);
-  const int64_t roff = (int64_t)row * kN + k;   // row-major offset of the same kE elements
+  frag::pk16_coords((size_t)off, kN, &row, &k);
+  // row-major offset of the same elements: runs of four, 8 apart
+  const int64_t roff = (int64_t)row * kN + k;
   float st[kE];
 #pragma unroll
   for (int i = 0; i < kE; ++i) st[i] = 0.0f;
   if (init) {
 #pragma unroll
     for (int i = 0; i < kV; ++i) {
-      const float4 f = reinterpret_cast<const float4*>(init + bh * kSlab + roff)[i];
+      const float4 f = *reinterpret_cast<const float4*>(init + bh * kSlab + roff + 8 * i);
       st[4 * i] = f.x; st[4 * i + 1] = f.y; st[4 * i + 2] = f.z; st[4 * i + 3] = f.w;
     }
   }
   const size_t cstride = (size_t)H * kSlab;
-  const size_t base = ((size_t)b * nc * H + h) * kSlab + off;
+  const size_t base = ((size_t)b * nc * H + h) * kSlab;
   const float* drow = dec + bh * nc;
   for (int c0 = 0; c0 < nc; c0 += kDepth) {
     float4 v[kDepth][kV];
@@ -191,7 +194,8 @@ __global__ __launch_bounds__(256) void fp16_pass_kernel(
       if (c0 + q < nc) {
 #pragma unroll
         for (int i = 0; i < kV; ++i)
-          v[q][i] = reinterpret_cast<const float4*>(S + base + (size_t)(c0 + q) * cstride)[i];
+          v[q][i] = *reinterpret_cast<const float4*>(S + base + soff + 256 * i +
+                                                     (size_t)(c0 + q) * cstride);
         d[q] = drow[c0 + q];
       }
     }
@@ -201,7 +205,7 @@ __global__ __launch_bounds__(256) void fp16_pass_kernel(
         uint32_t o[2 * kV];
 #pragma unroll
         for (int i = 0; i < 2 * kV; ++i) o[i] = pack_h2(st[2 * i], st[2 * i + 1]);
-        _Float16* dst = pin + base + (size_t)(c0 + q) * cstride;
+        _Float16* dst = pin + base + off + (size_t)(c0 + q) * cstride;
         if constexpr (kV == 2)
           *reinterpret_cast<uint4*>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
         else
@@ -219,7 +223,7 @@ __global__ __launch_bounds__(256) void fp16_pass_kernel(
   if (final_state) {
 #pragma unroll
     for (int i = 0; i < kV; ++i)
-      reinterpret_cast<float4*>(final_state + bh * kSlab + roff)[i] =
+      *reinterpret_cast<float4*>(final_state + bh * kSlab + roff + 8 * i) =
           make_float4(st[4 * i], st[4 * i + 1], st[4 * i + 2], st[4 * i + 3]);
   }
 }

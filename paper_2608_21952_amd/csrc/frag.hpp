@@ -90,5 +90,25 @@ __host__ __device__ __forceinline__ void k16_coords(size_t off, int K, int* row,
   *k = (int)(tile % kt) * 16 + 8 * (lane >> 5) + (int)(off & 7);
 }
 
+// Permuted k16 order (pk16): the same tiles, with the 16 K values dealt to the two half-waves in
+// runs of 4: lane l holds, in slot e, k = 8 (e / 4) + 4 (l / 32) + e % 4.  As with pk above, a
+// 32x32 MFMA result whose rows are K leaves its lanes in exactly this order (registers 8 kb .. 8
+// kb + 7 are the slots of K block kb), so chunk states go from accumulators to memory, or to the
+// operand of the next product, without a transpose.  C is permuted alike.
+__host__ __device__ __forceinline__ size_t pk16_offset(int row, int k, int K) {
+  const int kk = k & 15;
+  const int lane = (row & 31) + 32 * ((kk >> 2) & 1);
+  return ((size_t)(row >> 5) * (K >> 4) + (k >> 4)) * 512 + lane * 8 + 4 * (kk >> 3) + (kk & 3);
+}
+
+// Inverse of pk16_offset.
+__host__ __device__ __forceinline__ void pk16_coords(size_t off, int K, int* row, int* k) {
+  const size_t tile = off >> 9;
+  const int kt = K >> 4;
+  const int lane = (int)((off >> 3) & 63), e = (int)(off & 7);
+  *row = (int)(tile / kt) * 32 + (lane & 31);
+  *k = (int)(tile % kt) * 16 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+}
+
 }  // namespace frag
 }  // namespace ssdi8
