@@ -23,7 +23,7 @@ LIB = os.path.join(PKG, "libssdi8.so")
 ARCH = "gfx950"
 SOURCES = ["api.hip", "quantize.hip", "chunk_bmm.hip", "chunk_state.hip", "state_pass.hip",
            "chunk_scan.hip", "decode.hip", "fp16_bmm.hip", "fp16_state.hip",
-           "fp16_scan.hip", "calibrate.hip", "probe.hip"]
+           "fp16_scan.hip", "fp16_walk.hip", "calibrate.hip", "probe.hip"]
 
 # -ffp-contract=off: no fused multiply-add where the arithmetic defines separate roundings.
 # -packed-fp32-ops off: never emit packed fp32 arithmetic.
@@ -35,7 +35,8 @@ FLAGS = [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=
 # Per-source additions.  chunk_scan.hip: no wave-aggregated atomics, so that the single pass's
 # ticket atomic returns in the background while the loads issued after it are in flight (the
 # aggregated form reads its result, and waits for it, right away).
-SOURCE_FLAGS = {"chunk_scan.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]}
+SOURCE_FLAGS = {"chunk_scan.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"],
+                "fp16_walk.hip": ["-mllvm", "-disable-machine-licm"]}
 
 
 def flags_for(src: str) -> list:

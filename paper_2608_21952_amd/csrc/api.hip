@@ -118,6 +118,13 @@ Fp16Plan plan_fp16(const ssdi8_dims* d) {
   return p;
 }
 
+// Whether the FP16 layer's ChunkState and StatePassing run as the kernel that walks the sequences:
+// its chunks are serial, so it takes enough of them in flight.  Whole layer, separate / walk, slow
+// heads included: 48 sequences x 32 chunks 81 / 118 us, 80 x 64 267 / 311, 96 x 16 80 / 85,
+// 96 x 32 169 / 149, 112 x 32 196 / 170, 128 x 128 814 / 775, 192 x 8 84 / 76, 320 x 16 257 / 216,
+// 640 x 8 260 / 193, 1024 x 1 61 / 55.
+bool fp16_walks(const LayerDims& ld) { return (int64_t)ld.batch * ld.nheads >= 112; }
+
 struct CalibPlan {
   Fp16Plan f16;
   Plan i8;
@@ -472,11 +479,17 @@ ssdi8_status ssdi8_ssd_chunk_scan_fp16(const ssdi8_dims* d, const ssdi8_fp16_arg
   hipError_t e = ssdi8::launch_fp16_bmm(ld, a->C, a->B, a->bc_dtype, cb, bT, c16, cbmax,
                                           nullptr, st);
   if (e != hipSuccess || !mark(1)) return SSDI8_ERR_HIP;
-  e = ssdi8::launch_fp16_state(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, bT, S, dec,
-                               st);
-  if (e != hipSuccess || !mark(2)) return SSDI8_ERR_HIP;
-  e = ssdi8::launch_fp16_pass(ld, S, dec, a->init_state, pin, a->final_state, st);
-  if (e != hipSuccess || !mark(3)) return SSDI8_ERR_HIP;
+  if (fp16_walks(ld)) {
+    e = ssdi8::launch_fp16_walk(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, bT,
+                                a->init_state, pin, a->final_state, st);
+    if (e != hipSuccess || !mark(2) || !mark(3)) return SSDI8_ERR_HIP;
+  } else {
+    e = ssdi8::launch_fp16_state(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, bT, S, dec,
+                                 st);
+    if (e != hipSuccess || !mark(2)) return SSDI8_ERR_HIP;
+    e = ssdi8::launch_fp16_pass(ld, S, dec, a->init_state, pin, a->final_state, st);
+    if (e != hipSuccess || !mark(3)) return SSDI8_ERR_HIP;
+  }
   e = ssdi8::launch_fp16_scan(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, c16, pin, cb,
                               cbmax, a->D, a->y, a->y_dtype, st);
   if (e != hipSuccess || !mark(4)) return SSDI8_ERR_HIP;
@@ -558,10 +571,14 @@ ssdi8_status ssdi8_calibrate(const ssdi8_dims* d, const ssdi8_calib_args* a, voi
     e = ssdi8::launch_calib_steps(xs_amax, s_amax, cb_amax, a->xs_scale, a->state_scale,
                                   a->cb_scale, H, G, a->xs_per_head, st);
   // Y_fp: the FP16 layer (its ChunkBMM outputs are already in place)
-  if (e == hipSuccess)
+  if (e == hipSuccess && fp16_walks(ld)) {
+    e = ssdi8::launch_fp16_walk(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, bT, nullptr,
+                                pin16, nullptr, st);
+  } else if (e == hipSuccess) {
     e = ssdi8::launch_fp16_state(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, bT, S, dec,
                                  st);
-  if (e == hipSuccess) e = ssdi8::launch_fp16_pass(ld, S, dec, nullptr, pin16, nullptr, st);
+    if (e == hipSuccess) e = ssdi8::launch_fp16_pass(ld, S, dec, nullptr, pin16, nullptr, st);
+  }
   if (e == hipSuccess)
     e = ssdi8::launch_fp16_scan(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, c16, pin16,
                                 cb, cbmax, a->D, yfp, SSDI8_F32, st);

@@ -27,6 +27,19 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base) 
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)0xffffffffu,
                                            0x00020000);
 }
+// The same from a base that is wave-uniform but may sit in vector registers (64-bit products
+// run on the vector unit): moved to scalar registers once, where the compiler would otherwise
+// wrap every access in a loop over the wave's distinct bases.  `bytes`: the resource's range (0:
+// loads return zeros and read nothing).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const void* base,
+                                                               uint32_t bytes = 0xffffffffu) {
+  const uint64_t u = (uint64_t)(uintptr_t)base;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(uintptr_t)(((uint64_t)hi << 32) | lo), (short)0,
+      __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+}
 __device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff,
                                             uint32_t soff) {
   const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0);
@@ -248,12 +261,11 @@ constexpr int kScanScratch = 6;
 static __device__ __noinline__ double exact_sum_f32_outlined(const float* v, int n) {
   return exact_sum_f32(v, n);
 }
-template <bool kOutlined = false>
-__device__ __forceinline__ double block_scan_f64_256(float term, double* scratch, float* stage) {
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  double v = (double)term;
-  uint32_t er = exp_range_f32(term);
+// Its two halves, for blocks in which only four of the waves hold terms: the scan within a wave,
+// with the packed exponent range of the wave's terms in lane 63, ...
+__device__ __forceinline__ void wave_scan_f64(float term, double& v, uint32_t& er) {
+  v = (double)term;
+  er = exp_range_f32(term);
   v = dpp_add_f64<0x111, 0xf>(v);
   v = dpp_add_f64<0x112, 0xf>(v);
   v = dpp_add_f64<0x114, 0xf>(v);
@@ -266,15 +278,27 @@ __device__ __forceinline__ double block_scan_f64_256(float term, double* scratch
   er = dpp_max_u16x2<0x118, 0xf>(er);
   er = dpp_max_u16x2<0x142, 0xa>(er);
   er = dpp_max_u16x2<0x143, 0xc>(er);
+}
+// ... and the exactness test over the ranges of the four waves.
+__device__ __forceinline__ bool scan_is_exact(const uint32_t* sr) {
+  const uint32_t r = max_u16x2(max_u16x2(sr[0], sr[1]), max_u16x2(sr[2], sr[3]));
+  const int e_max = (int)(r & 0xffffu) - 256, e_min = 256 - (int)(r >> 16);
+  return r == 0u || e_max - e_min <= 21;
+}
+template <bool kOutlined = false>
+__device__ __forceinline__ double block_scan_f64_256(float term, double* scratch, float* stage) {
+  const int lane = threadIdx.x & 63;
+  const int w = threadIdx.x >> 6;
+  double v;
+  uint32_t er;
+  wave_scan_f64(term, v, er);
   uint32_t* sr = reinterpret_cast<uint32_t*>(scratch + 4);
   if (lane == 63) {
     scratch[w] = v;
     sr[w] = er;
   }
   __syncthreads();
-  const uint32_t r = max_u16x2(max_u16x2(sr[0], sr[1]), max_u16x2(sr[2], sr[3]));
-  const int e_max = (int)(r & 0xffffu) - 256, e_min = 256 - (int)(r >> 16);
-  if (r == 0u || e_max - e_min <= 21) {
+  if (scan_is_exact(sr)) {
     double pre = 0.0;
     for (int i = 0; i < w; ++i) pre += scratch[i];
     return v + pre;

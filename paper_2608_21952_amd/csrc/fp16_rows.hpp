@@ -1,0 +1,259 @@
+// Device code shared by the FP16 layer's scan kernels: the raw x pairs, ChunkScan's decay tables
+// and one row block (32 tokens) of ChunkScan2 on top of a ChunkScan1 product.
+#pragma once
+
+#include "common.hpp"
+#include "frag.hpp"
+
+namespace ssdi8 {
+namespace fp16 {
+
+constexpr int kXTS = kQ * 2 + 16;     // bytes per channel row of x^T (fp16)
+// A diagonal block whose decay span stays below this bound splits its decay without overflow.
+constexpr float kDiagSpan = 64.0f;
+
+typedef float f2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_h2(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2_t){a, b}, h2_t));
+}
+
+// Two adjacent channels of one token row, loaded raw.
+template <typename XT> struct Pair;
+template <> struct Pair<_Float16> {
+  typedef uint32_t raw;
+  template <int kPol = 0>
+  static __device__ __forceinline__ raw load(__amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so) {
+    return buf_load4<kPol>(r, vo, so);
+  }
+  static __device__ __forceinline__ uint16_t lo(raw v) { return (uint16_t)(v & 0xffffu); }
+  static __device__ __forceinline__ uint16_t hi(raw v) { return (uint16_t)(v >> 16); }
+  static __device__ __forceinline__ float lof(raw v) {
+    return (float)__builtin_bit_cast(_Float16, lo(v));
+  }
+  static __device__ __forceinline__ float hif(raw v) {
+    return (float)__builtin_bit_cast(_Float16, hi(v));
+  }
+};
+template <> struct Pair<float> {
+  typedef float2 raw;
+  template <int kPol = 0>
+  static __device__ __forceinline__ raw load(__amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so) {
+    const uint2 v = buf_load8<kPol>(r, vo, so);
+    return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+  }
+  static __device__ __forceinline__ uint16_t lo(raw v) {
+    return __builtin_bit_cast(uint16_t, (_Float16)v.x);
+  }
+  static __device__ __forceinline__ uint16_t hi(raw v) {
+    return __builtin_bit_cast(uint16_t, (_Float16)v.y);
+  }
+  static __device__ __forceinline__ float lof(raw v) { return v.x; }
+  static __device__ __forceinline__ float hif(raw v) { return v.y; }
+};
+
+// ChunkScan's decay tables of a chunk (r_t = cs at the last token of 32-token block t, r_{-1} = 0).
+struct Tables {
+  float u[kQ];         // dt_i exp(r_I - cs_i)                          (off-diagonal blocks)
+  float dg[kQ];        // dt_i exp(r_{I-1} - cs_i) if block I has a small span, else dt_i
+  float csr[kQ];       // cs_i - r_{I-1}
+  float R[8][8];       // exp(r_a - r_b), b <= a
+  float umax[8];       // max |u_i| over block I (inf if one is NaN)
+  double r[8];
+};
+
+// The tables' entries of token t (threads 0 .. 255); r is complete.
+__device__ __forceinline__ void build_tables(Tables& T, int t, float dtv, double cs) {
+  const int blk = t >> 5;
+  const double rprev = blk ? T.r[blk - 1] : 0.0;
+  const float u = dtv * expf((float)(T.r[blk] - cs));
+  T.u[t] = u;
+  float um = u == u ? __builtin_fabsf(u) : __builtin_inff();
+#pragma unroll
+  for (int o = 1; o < 32; o <<= 1) um = __builtin_fmaxf(um, __shfl_xor(um, o));
+  if ((t & 31) == 0) T.umax[blk] = um;
+  const float csr = (float)(cs - rprev);
+  T.csr[t] = csr;
+  const bool small_span = (float)(T.r[blk] - rprev) >= -kDiagSpan;
+  T.dg[t] = small_span ? dtv * expf(__builtin_fminf(-csr, kDiagSpan)) : dtv;
+  if (t < 64) {
+    const int ra = t >> 3, rb = t & 7;
+    T.R[ra][rb] = (rb <= ra) ? expf((float)(T.r[ra] - T.r[rb])) : 0.0f;
+  }
+}
+
+// The maximum this lane contributes to row block jt's skip test (lane & 7 = block), for row_block.
+__device__ __forceinline__ float block_max(const float* cb_max_cg, int jt, int lane) {
+  const int k = lane & 7;
+  return cb_max_cg[frag::cb_block(jt, 0) + (k < jt ? k : 0)];
+}
+
+// Row block jt on its ChunkScan1 product: y = Y1 exp(cs_j) + D x, then Scan2 over the causal
+// blocks on top.  Lane l: token row j = 32 jt + l % 32; register r of y0 / y1 holds channel p = 32
+// pt + 8 (r / 4) + 4 (l / 32) + r % 4.  cbrs: the chunk-group's fp32 CB blocks; cbm: block_max;
+// xg: fp32 x of the chunk and head (the D skip of an fp32 x is not rounded), token stride HP.
+// late() runs after the last CB load is issued: loads for what comes next belong there, since
+// vector loads complete in order.
+template <typename XT, typename F>
+__device__ __forceinline__ void row_block(int jt, int lane, const Tables& T, const uint8_t* xT,
+                                          __amdgpu_buffer_rsrc_t cbrs, float cbm, const XT* xg,
+                                          size_t HP, float Dh, v16f& y0, v16f& y1, F&& late) {
+  asm volatile("" : "+s"(jt) :: "memory");
+  const int pc = lane & 31, half = lane >> 5;
+  const uint32_t lane64 = lane * 64;
+  const int jrow = jt * 32 + pc;
+  const float csrj = T.csr[jrow];
+  const float ej = __expf(csrj);
+  // exp(cs_j) = exp(cs_j - r_{J-1}) exp(r_{J-1})
+  const float eo = ej * (jt ? __expf((float)T.r[jt - 1]) : 1.0f);
+#pragma unroll
+  for (int pt = 0; pt < 2; ++pt) {
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {
+      const int pb = pt * 32 + 8 * g4 + 4 * half;
+      float xv[4];
+      if constexpr (sizeof(XT) == 2) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          xv[q] = (float)*reinterpret_cast<const _Float16*>(xT + (pb + q) * kXTS + jrow * 2);
+      } else {
+        const float4 xf = *reinterpret_cast<const float4*>(xg + (size_t)jrow * HP + pb);
+        xv[0] = xf.x; xv[1] = xf.y; xv[2] = xf.z; xv[3] = xf.w;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int r = 4 * g4 + q;
+        if (pt) y1[r] = __builtin_fmaf(y1[r], eo, Dh * xv[q]);
+        else y0[r] = __builtin_fmaf(y0[r], eo, Dh * xv[q]);
+      }
+    }
+  }
+  // Leading off-diagonal blocks whose every weight rounds to an fp16 zero are skipped: |W| <=
+  // max |CB| max |u| R (e_j <= 1), and below 2^-26 (half the smallest fp16 subnormal is 2^-25) it
+  // is zero.
+  const uint32_t cbrow = frag::cb_block(jt, 0) * 4096;
+  const bool diag_fast =
+      __builtin_amdgcn_readfirstlane((int)(T.csr[jt * 32 + 31] >= -kDiagSpan)) != 0;
+  int it0 = jt;
+  {
+    const int k = lane & 7;
+    const bool live = k < jt && !(cbm * T.umax[k] * T.R[jt ? jt - 1 : 0][k] < 0x1p-26f);
+    const uint32_t lv = (uint32_t)__ballot(live) & 0xffu;
+    if (lv) it0 = (int)__builtin_ctz(lv);
+    it0 = __builtin_amdgcn_readfirstlane(it0);
+  }
+  auto mfma_block = [&](const float (&wv)[8], int i0) {
+    v8h wf;
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      const h2_t hh = __builtin_convertvector((f2_t){wv[e], wv[e + 1]}, h2_t);
+      wf[e] = hh.x;
+      wf[e + 1] = hh.y;
+    }
+    const v8h xa0 = *reinterpret_cast<const v8h*>(xT + pc * kXTS + i0 * 2);
+    const v8h xa1 = *reinterpret_cast<const v8h*>(xT + (32 + pc) * kXTS + i0 * 2);
+    y0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa0, wf, y0, 0, 0, 0);
+    y1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa1, wf, y1, 0, 0, 0);
+  };
+  auto load_block = [&](uint32_t off, uint4 (&v)[4]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = buf_load16(cbrs, lane64, off + 16 * u);
+  };
+  auto cbv = [](const uint4 (&v)[4], int k) {   // float k of this lane's 16
+    const uint4 q = v[k >> 2];
+    const uint32_t e = (k & 3) == 0 ? q.x : (k & 3) == 1 ? q.y : (k & 3) == 2 ? q.z : q.w;
+    return __uint_as_float(e);
+  };
+  uint4 cur[4];
+  load_block(cbrow + it0 * 4096, cur);
+  for (int it = it0; it < jt; ++it) {
+    uint4 nx[4];
+    load_block(cbrow + (it + 1) * 4096, nx);
+    __builtin_amdgcn_sched_barrier(0);
+    const float vj = ej * T.R[jt - 1][it];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int i0 = it * 32 + ks * 16 + 8 * half;
+      float wv[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) wv[e] = (cbv(cur, 8 * ks + e) * T.u[i0 + e]) * vj;
+      mfma_block(wv, i0);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) cur[u] = nx[u];
+  }
+  late();
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int i0 = jt * 32 + ks * 16 + 8 * half;
+    float wv[8];
+    if (diag_fast) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float v = (cbv(cur, 8 * ks + e) * T.dg[i0 + e]) * ej;
+        wv[e] = (i0 + e <= jrow) ? v : 0.0f;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float ex = __expf(__builtin_fminf(csrj - T.csr[i0 + e], 0.0f));
+        const float v = (cbv(cur, 8 * ks + e) * T.dg[i0 + e]) * ex;
+        wv[e] = (i0 + e <= jrow) ? v : 0.0f;
+      }
+    }
+    mfma_block(wv, i0);
+  }
+}
+
+// A row block's fp16 output in the stage of 256 rows of 128 bytes: row j at 128 j, its 16-byte
+// chunk k at slot k ^ (j & 7) (conflict-free writes by token and reads by row).
+__device__ __forceinline__ void stage_rows_f16(uint8_t* s_y, int jt, int lane, const v16f& y0,
+                                               const v16f& y1) {
+  const uint32_t pc = lane & 31;
+  uint8_t* row = s_y + (jt * 32 + pc) * 128 + 8 * (lane >> 5);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int r = 4 * (k & 3);
+    const v16f& v = k < 4 ? y0 : y1;
+    *reinterpret_cast<uint2*>(row + (k ^ (pc & 7)) * 16) =
+        make_uint2(pack_h2(v[r], v[r + 1]), pack_h2(v[r + 2], v[r + 3]));
+  }
+}
+// The same for fp32 output, 128 rows of 256 bytes (blocks 0..3 or 4..7; jt4 = block % 4): 16-byte
+// chunk k at slot k ^ (j & 15).
+__device__ __forceinline__ void stage_rows_f32(uint8_t* s_y, int jt4, int lane, const v16f& y0,
+                                               const v16f& y1) {
+  const uint32_t pc = lane & 31, half = lane >> 5;
+  uint8_t* row = s_y + (jt4 * 32 + pc) * 256;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int r = 4 * (k & 3);
+    const v16f& v = k < 4 ? y0 : y1;
+    *reinterpret_cast<float4*>(row + ((2 * k + half) ^ (pc & 15)) * 16) =
+        make_float4(v[r], v[r + 1], v[r + 2], v[r + 3]);
+  }
+}
+// Rows [row0, row0 + rows) of the chunk leave the stage as whole rows (kRB bytes each: 128 or
+// 256), by kThreads threads; yrs: y of the chunk and head, token stride HP elements.
+template <int kRB, int kThreads>
+__device__ __forceinline__ void rows_out(const uint8_t* s_y, __amdgpu_buffer_rsrc_t yrs, int t,
+                                         size_t HP, int row0, int stream) {
+  constexpr int kC = kRB / 16;              // 16-byte chunks per row
+  constexpr int kRows = kThreads / kC;      // rows per step
+  constexpr int kSteps = (kQ * kP * 2) / (16 * kThreads);   // the stage holds 32 KB
+  const int row = t / kC, col = t % kC;
+  const uint8_t* src = s_y + row * kRB + ((col ^ (row & (kC - 1))) * 16);
+  const uint32_t es = kRB / kP;             // bytes per element
+  const uint32_t yo = (uint32_t)(row * HP * es + col * 16);
+#pragma unroll
+  for (int k = 0; k < kSteps; ++k) {
+    const uint4 v = *reinterpret_cast<const uint4*>(src + k * kRows * kRB);
+    const uint32_t so = (uint32_t)((row0 + kRows * k) * HP * es);
+    if (stream) buf_store16<kPolicyNT>(v, yrs, yo, so);
+    else buf_store16(v, yrs, yo, so);
+  }
+}
+static_assert(kP * kXTS >= kQ * kP * 2, "the output stages reuse the x^T bytes");
+
+}  // namespace fp16
+}  // namespace ssdi8

@@ -10,6 +10,7 @@
 // in which the accumulators hold it, so that every store covers a contiguous 1 KB); the initial
 // and final states are row-major [p][n].
 #include "common.hpp"
+#include "fp16_rows.hpp"
 #include "frag.hpp"
 #include "launch.hpp"
 
@@ -144,12 +145,6 @@ __global__ __launch_bounds__(256) void fp16_state_kernel(
 // per thread, kDepth chunks of loads in flight.  The running state stays fp32 in registers; what
 // is written is ChunkScan1's operand, fp16(P_in[c]) (6 instead of 8 bytes per element of HBM
 // traffic, which bounds it: 54 -> 41 us on the 2.7B-shaped layer).
-typedef float f2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack_h2(float a, float b) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2_t){a, b}, h2_t));
-}
-
 template <int kV>   // float4 per thread
 __global__ __launch_bounds__(256) void fp16_pass_kernel(
     const float* __restrict__ S, const float* __restrict__ dec, const float* __restrict__ init,
@@ -204,7 +199,7 @@ __global__ __launch_bounds__(256) void fp16_pass_kernel(
       if (c0 + q < nc) {
         uint32_t o[2 * kV];
 #pragma unroll
-        for (int i = 0; i < 2 * kV; ++i) o[i] = pack_h2(st[2 * i], st[2 * i + 1]);
+        for (int i = 0; i < 2 * kV; ++i) o[i] = fp16::pack_h2(st[2 * i], st[2 * i + 1]);
         _Float16* dst = pin + base + off + (size_t)(c0 + q) * cstride;
         if constexpr (kV == 2)
           *reinterpret_cast<uint4*>(dst) = make_uint4(o[0], o[1], o[2], o[3]);

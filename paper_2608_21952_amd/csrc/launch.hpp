@@ -150,6 +150,12 @@ hipError_t launch_fp16_scan(const LayerDims& d, const void* x, int x_dtype, cons
                             const _Float16* pin, const float* cb, const float* cb_max,
                             const float* D, void* y, int y_dtype, hipStream_t st);
 
+// ChunkState and state passing as one kernel walking each sequence (no chunk states in memory).
+hipError_t launch_fp16_walk(const LayerDims& d, const void* x, int x_dtype, const float* dt,
+                            int dt_softplus, const float* A, const _Float16* bT_frag,
+                            const float* init, _Float16* pin, float* final_state,
+                            hipStream_t st);
+
 // Calibration (static steps and the mean correction): absmax words cleared by a fill kernel,
 // absmax of X_scaled, fp states from split fp16 operands with their absmax, the steps, the
 // correction from two fp32 layer outputs.

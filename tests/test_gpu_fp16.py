@@ -125,3 +125,29 @@ def test_fp16_scan_edges(torch, ssdi8, batch, seqlen, nheads, ngroups, dtype, y_
     for (b, h) in picks:
         assert_close(y[b, :, h], ref["slabs"][(b, h)]["y64"], f"y slab ({b},{h})")
         _check_state(fin[b, h], ref["slabs"][(b, h)]["final"], f"final state slab ({b},{h})")
+
+
+@pytest.mark.parametrize("batch,seqlen,nheads,ngroups,dtype,init", [
+    (2, 256, 56, 1, "fp16", True),      # the fewest sequences walked, one chunk
+    (1, 768, 113, 1, "fp32", False),    # odd chunks and heads, one chunk of x ahead
+    (4, 1024, 30, 5, "fp16", True),     # even chunks, groups
+    (1, 512, 111, 3, "fp16", True),     # one sequence too few: the separate kernels
+])
+def test_fp16_walk_matches_oracle(torch, ssdi8, batch, seqlen, nheads, ngroups, dtype, init):
+    """ChunkState and StatePassing as one walk over each sequence: odd and even chunk counts, both
+    x types, an initial state, and a chunk whose dt spans over 21 binades (the exact scan)."""
+    cfg = dataclasses.replace(synth.CONFIGS["mamba2-130m"], name="fp16-walk", batch=batch,
+                              seqlen=seqlen, nheads=nheads, ngroups=ngroups, dtype=dtype,
+                              a_lo=-4.0)
+    inp = synth.draw(cfg, 1)
+    inp["dt_raw"][0, :256:3, 0] = -18.0   # softplus 1.5e-8 beside 0.1
+    rng = np.random.default_rng(6)
+    st = rng.standard_normal((batch, nheads, 64, 128)).astype(np.float32) if init else None
+    g = _run(torch, ssdi8, inp, init=st)
+    y, fin = g["y"].float().cpu().numpy(), g["final_state"].cpu().numpy()
+    picks = sorted({(0, 0), (batch - 1, nheads - 1), (batch // 2, nheads // 2)})
+    ref = ofp.ssd_fp16_forward(inp["x"], inp["dt_raw"], inp["A"], inp["B"], inp["C"], inp["D"],
+                               chunk=cfg.chunk, heads=picks, init=st)
+    for (b, h) in picks:
+        assert_close(y[b, :, h], ref["slabs"][(b, h)]["y64"], f"y slab ({b},{h})")
+        _check_state(fin[b, h], ref["slabs"][(b, h)]["final"], f"final state slab ({b},{h})")
