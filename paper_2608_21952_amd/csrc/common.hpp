@@ -123,6 +123,26 @@ __device__ __forceinline__ uint32_t pass_step4_pk16(uint32_t p, uint32_t s, s16x
                                0x06020400u);
 }
 
+// The same with the chunk-local codes as quant_bits leaves them (their low 16 bits are the int16
+// value), one word per element.
+__device__ __forceinline__ uint32_t pass_step4_pk16_q(uint32_t p, const uint32_t (&sq)[4], int q,
+                                                      int radd, int shift) {
+  const s16x2 eight = {8, 8};
+  const s16x2 q2 = {(short)q, (short)q}, r2 = {(short)radd, (short)radd};
+  const s16x2 k2 = {(short)shift, (short)shift};
+  const s16x2 pe = __builtin_bit_cast(s16x2, p << 8) >> eight;
+  const s16x2 po = __builtin_bit_cast(s16x2, p) >> eight;
+  const s16x2 se = __builtin_bit_cast(s16x2, __builtin_amdgcn_perm(sq[2], sq[0], 0x05040100u));
+  const s16x2 so = __builtin_bit_cast(s16x2, __builtin_amdgcn_perm(sq[3], sq[1], 0x05040100u));
+  const s16x2 lo = {-kQMax, -kQMax}, hi = {kQMax, kQMax};
+  s16x2 ve = se + ((q2 * pe + r2) >> k2);
+  s16x2 vo = so + ((q2 * po + r2) >> k2);
+  ve = __builtin_elementwise_max(__builtin_elementwise_min(ve, hi), lo);
+  vo = __builtin_elementwise_max(__builtin_elementwise_min(vo, hi), lo);
+  return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, vo), __builtin_bit_cast(uint32_t, ve),
+                               0x06020400u);
+}
+
 // The low bytes of four words in one dword (byte i = low byte of w_i): two byte permutes and a
 // shift-or.
 __device__ __forceinline__ uint32_t pack_lo4(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {

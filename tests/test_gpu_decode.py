@@ -154,3 +154,38 @@ def test_decode_empty_batch(torch, ssdi8):
     out = ssdi8.decode_step(torch.zeros((0, 4, 64), dtype=torch.float16, device="cuda"),
                             z(0, 4), z(4), q, q, z(2), z(2), z(4, 64), z(4, 64), z(2), st)
     assert out["y"].shape == (0, 4, 64)
+
+
+@pytest.mark.parametrize("batch,nheads,ngroups,shift,x_dtype", [
+    (39, 80, 2, 7, "fp16"),     # runs of two batch elements, the last of one
+    (33, 125, 5, 8, "fp32"),    # runs of four, the last of one; the widest packed shift
+    (131, 63, 3, 9, "fp16"),    # runs of eight, the last of three; the 32-bit step
+    (47, 65, 1, 7, "fp16"),     # one element per workgroup, just below runs
+])
+def test_decode_runs_of_batch_elements(torch, ssdi8, batch, nheads, ngroups, shift, x_dtype):
+    """Large batches: several batch elements per workgroup, ragged last runs, both state steps."""
+    cfg = _cfg("decode-runs", batch=batch, seqlen=256, nheads=nheads, ngroups=ngroups,
+               dtype=x_dtype)
+    small = dataclasses.replace(cfg, batch=1)
+    sc = calibration(small)
+    rng = np.random.default_rng(8)
+    st = synth.structure(cfg)
+    x = rng.standard_normal((batch, 1, nheads, 64)).astype(
+        np.float16 if x_dtype == "fp16" else np.float32)
+    inp = {"x": x, "A": st["A"], "D": st["D"],
+           "B": rng.standard_normal((batch, 1, ngroups, 128)).astype(np.float16),
+           "C": rng.standard_normal((batch, 1, ngroups, 128)).astype(np.float16),
+           "dt_raw": rng.normal(-3, 1, (batch, 1, nheads)).astype(np.float32)}
+    init = rng.integers(-127, 128, (batch, nheads, 64, 128)).astype(np.int8)
+    f = lambda v: dev(np.asarray(v, np.float32), torch)
+    state = dev(init, torch)
+    q = lambda k, a: ssdi8.quantize_act(dev(inp[k], torch), "group", f(sc[a]))[0][:, 0]
+    out = ssdi8.decode_step(dev(x[:, 0], torch), f(inp["dt_raw"][:, 0]), f(inp["A"]),
+                            q("B", "alpha_B").contiguous(), q("C", "alpha_C").contiguous(),
+                            f(sc["alpha_B"]), f(sc["alpha_C"]), f(sc["alpha_Xs"]),
+                            f(sc["alpha_S"]), f(sc["alpha_CB"]), state, D=f(inp["D"]),
+                            corr=f(sc["corr"]), decay_shift=shift)
+    ref = oq.ssdi8_forward(x, inp["dt_raw"], inp["A"], inp["B"], inp["C"], inp["D"], sc["corr"],
+                           sc, chunk=1, k=shift, init_q=init, want=("y64", "final_q"))
+    assert_equal(state.cpu().numpy(), ref["final_q"], "new state")
+    assert_close(out["y"].float().cpu().numpy(), ref["y64"][:, 0], "y")
