@@ -80,8 +80,11 @@ template <int kU>
 __global__ __launch_bounds__(256) void quant_static_h8(const _Float16* __restrict__ src,
                                                       int8_t* __restrict__ dst,
                                                       const float* __restrict__ scale, int gran,
-                                                      uint32_t nunit, uint32_t k, uint32_t m) {
+                                                      uint32_t nunit, uint32_t k, uint32_t m,
+                                                      int row_shift) {
   const uint32_t rowunits = m / 8;
+  // a single step is a scalar load under way before the data arrives
+  const float step0 = scale[0];
   const uint32_t u0 = blockIdx.x * (256u * kU) + threadIdx.x;
   uint4 raw[kU];
 #pragma unroll
@@ -93,7 +96,7 @@ __global__ __launch_bounds__(256) void quant_static_h8(const _Float16* __restric
   for (int u = 0; u < kU; ++u) {
     const uint32_t unit = u0 + 256u * u;
     if (unit >= nunit) break;
-    const uint32_t row = unit / rowunits;
+    const uint32_t row = row_shift >= 0 ? unit >> row_shift : unit / rowunits;
     const uint32_t w[4] = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
     uint32_t q[8];
     if (gran == 2) {
@@ -105,8 +108,7 @@ __global__ __launch_bounds__(256) void quant_static_h8(const _Float16* __restric
         q[i] = quant_bits(x, 1.0f / scale[c0 + i]);
       }
     } else {
-      const uint32_t gi = gran == 0 ? 0u : (gran == 1 ? row % k : row);
-      const float inv = 1.0f / scale[gi];
+      const float inv = 1.0f / (gran == 0 ? step0 : scale[gran == 1 ? row % k : row]);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const float x = (float)__builtin_bit_cast(
@@ -289,6 +291,38 @@ __global__ __launch_bounds__(256) void quant_token_dynamic(const T* __restrict__
   for (int64_t i = lane; i < m; i += 64) dst[row * m + i] = (int8_t)quant_i8((float)s[i], inv);
 }
 
+// The same for fp16 rows of m = 128 elements: 16 lanes hold a row, one 16-byte load each, so a
+// wave reads 1 KB at a time and the row's maximum takes four exchanges.
+__global__ __launch_bounds__(256) void quant_token_dynamic_h128(const _Float16* __restrict__ src,
+                                                                int8_t* __restrict__ dst,
+                                                                float* __restrict__ scale,
+                                                                uint32_t rows) {
+  const uint32_t unit = blockIdx.x * 256u + threadIdx.x, row = unit >> 4;
+  const bool live = row < rows;
+  uint4 raw = make_uint4(0u, 0u, 0u, 0u);
+  if (live) raw = reinterpret_cast<const uint4*>(src)[unit];
+  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+  float v[8], mx = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    v[i] = (float)__builtin_bit_cast(
+        _Float16, (uint16_t)((i & 1) ? (w[i >> 1] >> 16) : (w[i >> 1] & 0xffffu)));
+    mx = __builtin_fmaxf(mx, __builtin_fabsf(v[i]));
+  }
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) mx = __builtin_fmaxf(mx, __shfl_xor(mx, o, 64));
+  float a = mx / 127.0f;
+  a = (a == 0.0f) ? 1.0f : a;
+  if (!live) return;
+  if ((unit & 15u) == 0) scale[row] = a;
+  const float inv = 1.0f / a;
+  uint32_t q[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) q[i] = quant_bits(v[i], inv);
+  reinterpret_cast<uint2*>(dst)[unit] =
+      make_uint2(pack_lo4(q[0], q[1], q[2], q[3]), pack_lo4(q[4], q[5], q[6], q[7]));
+}
+
 // blocks of the dynamic absmax (several per CU for loads in flight; their partial maxima are
 // reduced by a second kernel, so more blocks cost no atomics)
 constexpr int64_t kAbsmaxBlocks = 512;
@@ -305,6 +339,12 @@ hipError_t quantize_impl(const T* src, int64_t b, int64_t l, int64_t k, int64_t 
   if (compute_scale && gran == 3) {
     const int64_t rows = b * l * k;
     if (rows == 0) return hipSuccess;
+    if (sizeof(T) == 2 && m == 128 && rows < ((int64_t)1 << 27)) {
+      hipLaunchKernelGGL(quant_token_dynamic_h128, dim3((unsigned)((rows + 15) / 16)), dim3(256),
+                         0, st, reinterpret_cast<const _Float16*>(src), dst, scale,
+                         (uint32_t)rows);
+      return hipGetLastError();
+    }
     hipLaunchKernelGGL(quant_token_dynamic<T>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0,
                        st, src, dst, scale, rows, m);
     return hipGetLastError();
@@ -356,11 +396,20 @@ hipError_t quantize_impl(const T* src, int64_t b, int64_t l, int64_t k, int64_t 
   }
   if (n == 0) return hipGetLastError();
   if (sizeof(T) == 2 && m % 8 == 0 && n < ((int64_t)1 << 31)) {
-    constexpr int kU = 4;
     const int64_t nunit = n / 8;
-    hipLaunchKernelGGL(quant_static_h8<kU>, dim3((unsigned)((nunit + 256 * kU - 1) / (256 * kU))),
-                       dim3(256), 0, st, reinterpret_cast<const _Float16*>(src), dst, scale, gran,
-                       (uint32_t)nunit, (uint32_t)k, (uint32_t)m);
+    const int64_t ru = m / 8;
+    const int row_shift = (ru & (ru - 1)) == 0 ? __builtin_ctzll(ru) : -1;
+    // one group is one step for the whole tensor
+    const int gr = gran == 1 && k == 1 ? 0 : gran;
+    // four units in flight per thread; tensors that leave the chip idle anyway take one, so that
+    // they spread over four times the threads
+#define SSDI8_QUANT_LAUNCH(U)                                                                   \
+  hipLaunchKernelGGL(quant_static_h8<U>, dim3((unsigned)((nunit + 256 * U - 1) / (256 * U))),   \
+                     dim3(256), 0, st, reinterpret_cast<const _Float16*>(src), dst, scale, gr,  \
+                     (uint32_t)nunit, (uint32_t)k, (uint32_t)m, row_shift)
+    if (nunit >= (1 << 20)) SSDI8_QUANT_LAUNCH(4);
+    else SSDI8_QUANT_LAUNCH(1);
+#undef SSDI8_QUANT_LAUNCH
   } else if (m % 16 == 0) {
     const int64_t nvec = n / 16;
     if (n < ((int64_t)1 << 31)) {

@@ -464,3 +464,32 @@ def test_mfma_probe_counts_and_runs(torch, ssdi8):
         torch.cuda.synchronize()
         assert st == 0 and ops.value == 8 * 4 * 4 * 100 * 2 * mnk
     assert ssdi8.mfma_peak("int8", iters=200, blocks=256, reps=1) > 0
+
+
+@pytest.mark.parametrize("shape,gran", [
+    ((1, 1, 1, 128), "token"), ((2, 9, 3, 128), "token"), ((1, 1027, 1, 128), "token"),
+    ((3, 5, 1, 24), "group"), ((1, 7, 8, 128), "group"), ((2, 33, 3, 40), "channel"),
+    ((1, 65536, 1, 128), "group"), ((1, 65537, 1, 128), "tensor"),
+])
+def test_quantize_fp16_row_kernels(torch, ssdi8, shape, gran):
+    """The fp16 kernels of 8-element units: one and four units per thread (from 2^20 units), row
+    lengths that are and are not powers of two, and the 128-wide per-token dynamic steps with
+    ragged last blocks, an all-zero row among them."""
+    rng = np.random.default_rng(11)
+    src = (rng.standard_normal(shape) * 3).astype(np.float16)
+    src[0, 0, 0] = 0
+    b, l, k, m = shape
+    if gran == "token":
+        q, s = ssdi8.quantize_act(dev(src, torch), "token")
+        amax = np.abs(src.astype(np.float32)).max(axis=3)
+        ref_s = (amax / np.float32(127)).astype(np.float32)
+        ref_s[ref_s == 0] = 1.0
+        assert_equal(s.cpu().numpy().reshape(b, l, k), ref_s, "steps")
+        step = ref_s[..., None]
+    else:
+        n = {"tensor": (1, 1), "group": (k, 1), "channel": (k, m)}[gran]
+        step = rng.uniform(0.01, 0.1, n).astype(np.float32)
+        q, _ = ssdi8.quantize_act(dev(src, torch), gran, dev(step.reshape(-1), torch))
+    inv = (np.float32(1) / step).astype(np.float32)
+    ref = np.clip(np.rint(src.astype(np.float32) * inv), -127, 127).astype(np.int8)
+    assert_equal(q.cpu().numpy(), ref, "codes")
