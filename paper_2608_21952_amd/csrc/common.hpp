@@ -309,16 +309,29 @@ template <bool kOutlined = false>
 __device__ __forceinline__ double block_scan_f64_256(float term, double* scratch, float* stage) {
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
-  double v;
-  uint32_t er;
-  wave_scan_f64(term, v, er);
+  double v = (double)term;
+  uint32_t er = exp_range_f32(term);
+  v = dpp_add_f64<0x111, 0xf>(v);
+  v = dpp_add_f64<0x112, 0xf>(v);
+  v = dpp_add_f64<0x114, 0xf>(v);
+  v = dpp_add_f64<0x118, 0xf>(v);
+  v = dpp_add_f64<0x142, 0xa>(v);
+  v = dpp_add_f64<0x143, 0xc>(v);
+  er = dpp_max_u16x2<0x111, 0xf>(er);
+  er = dpp_max_u16x2<0x112, 0xf>(er);
+  er = dpp_max_u16x2<0x114, 0xf>(er);
+  er = dpp_max_u16x2<0x118, 0xf>(er);
+  er = dpp_max_u16x2<0x142, 0xa>(er);
+  er = dpp_max_u16x2<0x143, 0xc>(er);
   uint32_t* sr = reinterpret_cast<uint32_t*>(scratch + 4);
   if (lane == 63) {
     scratch[w] = v;
     sr[w] = er;
   }
   __syncthreads();
-  if (scan_is_exact(sr)) {
+  const uint32_t r = max_u16x2(max_u16x2(sr[0], sr[1]), max_u16x2(sr[2], sr[3]));
+  const int e_max = (int)(r & 0xffffu) - 256, e_min = 256 - (int)(r >> 16);
+  if (r == 0u || e_max - e_min <= 21) {
     double pre = 0.0;
     for (int i = 0; i < w; ++i) pre += scratch[i];
     return v + pre;
