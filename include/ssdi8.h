@@ -166,9 +166,9 @@ typedef struct {
      sequence through the workspace (a flag per chunk; Eq. 9 applied in chunk order, so every
      integer result and y are bit-identical to the separate kernels).  The state_in_q tap is
      served by either path.  0: automatic (the single pass where it is the faster one, which
-     takes enough concurrent sequences to hide the serial hand-offs: batch * nheads >= 72 with
-     at least 4 chunks, or >= 48 with at least 32); 1: always the separate kernels; 2: the
-     single pass whenever eligible.
+     takes enough concurrent sequences to hide the serial hand-offs: batch * nheads >= 64 with
+     at least 4 chunks, or >= 48 with at least 32, or any number with 1 or 4 chunks); 1: always
+     the separate kernels; 2: the single pass whenever eligible.
      With the single pass, events 1-2 of stage_events mark the end of ChunkBMM and 3-4 the
      single pass's own start and end. */
   int path;

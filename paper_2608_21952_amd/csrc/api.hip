@@ -186,12 +186,13 @@ bool single_pass(const ssdi8_dims* d, const ssdi8_scan_args* a) {
   if (!eligible) return false;
   if (a->path != 0) return a->path == 2;
   // automatic: the single pass hides its chains of hand-offs behind enough concurrent sequences.
-  // Measured crossover on MI355X (130M-shaped layers, B H sequences of nc chunks), taken where
-  // the chains are longest (slowly decaying heads, no chunk with a zero Q(Decay)): it wins from
-  // 72 sequences at 4 chunks and more, and from 48 sequences at 32 chunks
+  // Taken where the chains are longest (slowly decaying heads, no chunk with a zero Q(Decay)).
+  // Layer us, separate / single: one chunk 28 / 23 (8 to 64 sequences; no hand-off), four chunks
+  // 28 / 26 (8), 28 / 27 (24), 32 / 29 (64); 8 chunks 30 / 32 (24); 16 chunks 48 / 50 (48), 53 / 53
+  // (56), 55 / 52 (64), 65 / 60 (80); 32 chunks 48 / 62 (24), 71 / 67 (48)
   const int64_t nc = d->chunk > 0 ? d->seqlen / d->chunk : 0;
   const int64_t bh = d->batch * d->nheads;
-  return (bh >= 72 && nc >= 4) || (bh >= 48 && nc >= 32);
+  return nc == 1 || nc == 4 || (bh >= 64 && nc >= 4) || (bh >= 48 && nc >= 32);
 }
 
 }  // namespace
