@@ -1,9 +1,10 @@
-"""Build libssdi8.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree.
+"""Build libssdi8.so (HIP kernels + C ABI) for gfx950 with hipcc, and the Python binding's native
+part (_binding.so, host C++ against PyTorch's headers), in-tree.
 
     python -m paper_2608_21952_amd.build          # or: from paper_2608_21952_amd.build import build
 
 Every call recompiles.  Objects go to _build/ at the repository root; the shared library is
-written next to this file (paper_2608_21952_amd/libssdi8.so) by an atomic rename.
+written next to this file (paper_2608_21952_amd/libssdi8.so, _binding.so) by an atomic rename.
 """
 from __future__ import annotations
 
@@ -12,6 +13,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -19,6 +21,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(ROOT, "_build", "ssdi8")
 LIB = os.path.join(PKG, "libssdi8.so")
+BINDING = os.path.join(PKG, "_binding.so")
 
 ARCH = "gfx950"
 SOURCES = ["api.hip", "quantize.hip", "chunk_bmm.hip", "chunk_state.hip", "state_pass.hip",
@@ -57,11 +60,31 @@ def _compile(src: str) -> str:
     return obj
 
 
+def build_binding() -> str:
+    """The native part of the Python binding: host code only, linked against PyTorch."""
+    import torch
+    from torch.utils import cpp_extension
+    tmp = BINDING + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-I{INCLUDE}", "-isystem", sysconfig.get_paths()["include"],
+           *[a for d in cpp_extension.include_paths() for a in ("-isystem", d)],
+           os.path.join(CSRC, "binding.cpp"), "-o", tmp,
+           f"-L{cpp_extension.TORCH_LIB_PATH}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for binding.cpp:\n{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, BINDING)
+    return BINDING
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJDIR, exist_ok=True)
     jobs = min(len(SOURCES), max(1, min(16, os.cpu_count() or 1)))
     with concurrent.futures.ThreadPoolExecutor(jobs) as ex:
+        binding = ex.submit(build_binding)
         objs = list(ex.map(_compile, SOURCES))
+        binding.result()
     tmp = LIB + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)

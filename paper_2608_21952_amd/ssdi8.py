@@ -4,6 +4,10 @@ Every step of the SSD path runs in the library's HIP kernels; this module checks
 placement/dtype/shape, allocates outputs and the workspace with PyTorch (device memory and
 streams are PyTorch's job here), and forwards raw device pointers and the current HIP stream.
 There is no fallback: if the shared library is missing or fails to load, every call raises.
+
+The per-layer and per-token calls marshal in native code (csrc/binding.cpp): the functions here hand
+plain arguments to it and keep the general form below, for taps, events, other argument types and
+the errors.
 """
 from __future__ import annotations
 
@@ -86,11 +90,12 @@ class CalibArgs(ctypes.Structure):
 
 
 _lib = None
+_native = None    # the native marshalling, loaded with the library
 
 
 def lib() -> ctypes.CDLL:
     """The loaded shared library (raises if it has not been built)."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -129,8 +134,31 @@ def lib() -> ctypes.CDLL:
     L.ssdi8_status_string.restype = ctypes.c_char_p
     L.ssdi8_version.argtypes = []
     L.ssdi8_version.restype = ctypes.c_char_p
+    addr = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    from . import _binding
+    _binding.bind(addr(L.ssdi8_quantize_act), addr(L.ssdi8_ssd_workspace_size),
+                  addr(L.ssdi8_ssd_chunk_scan), addr(L.ssdi8_decode_step))
+    _native = _binding
     _lib = L
     return L
+
+
+def _raw_stream(stream) -> Optional[int]:
+    """The stream as an integer for the native calls, None if it takes the general form."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    raw = stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
+    return raw if type(raw) is int else None
+
+
+_YCODE = {None: -1, torch.float32: F32, torch.float16: F16}
+
+
+def _plain(x) -> bool:
+    """Whether a native call may be tried: the library is loaded and x is a device tensor."""
+    if _native is None:
+        lib()
+    return type(x) is torch.Tensor and x.is_cuda
 
 
 def status_string(status: int) -> str:
@@ -182,6 +210,15 @@ def quantize_act(src: torch.Tensor, gran: str = "group", scale: Optional[torch.T
                  ) -> Tuple[torch.Tensor, torch.Tensor]:
     """Eq. 1 quantization of a (b, l, k, m) activation.  With `scale` the steps are static;
     without, they are computed on the device (absmax/127 per granule) and returned."""
+    code = GRAN.get(gran)
+    if code is not None and _plain(src):
+        st = _raw_stream(stream)
+        r = None if st is None else _native.quantize(src, code, scale, out, st)
+        if r is not None:
+            if r[0] != OK:
+                _check(r[0], "ssdi8_quantize_act")
+            # the caller's own tensors come back as they are
+            return (r[1] if out is None else out), (r[2] if scale is None else scale)
     _need(src, "src")
     if src.dim() != 4:
         raise ValueError("src must be (b, l, k, m)")
@@ -278,6 +315,22 @@ def ssd_chunk_scan(x: torch.Tensor, dt: torch.Tensor, A: torch.Tensor,
     single-pass kernel whenever x is fp16 and no stage tap other than state_in_q is requested).
     hand_off_timeouts: an int32 device tensor of one element, or None; receives the number of
     single-pass waits that ran out (non-zero: the results of the call are not to be used)."""
+    if not taps and stage_events is None and not _noalloc and path in PATHS \
+            and y_dtype in _YCODE and _plain(x):
+        raw = _raw_stream(stream)
+        r = None if raw is None else _native.scan(
+            x, dt, A, Bq, Cq, B, C, B_scale, C_scale, xs_scale, state_scale, cb_scale, D, corr,
+            init_state_q, y, _YCODE[y_dtype], workspace, hand_off_timeouts, int(dt_softplus),
+            chunk, int(decay_shift), int(shift_round), int(bool(final_state)), PATHS[path], raw)
+        if r is not None:
+            if r[0] != OK:
+                _check(r[0], "ssdi8_ssd_chunk_scan")
+            out = {"y": r[1] if y is None else y}
+            if final_state:
+                out["final_state_q"], out["final_state"] = r[2], r[3]
+            if hand_off_timeouts is not None:
+                out["hand_off_timeouts"] = hand_off_timeouts
+            return out
     _need(x, "x")
     Bsrc, Csrc = (Bq, Cq) if Bq is not None else (B, C)
     B, L, H, P = x.shape
@@ -515,6 +568,15 @@ def decode_step(x: torch.Tensor, dt: torch.Tensor, A: torch.Tensor, Bq: torch.Te
     """One decode token (ssdi8_decode_step): x (B,H,P), dt (B,H), Bq/Cq (B,G,N) int8, C_scale
     (G) or (B,G); state_q (B,H,P,N) int8 is updated in place.  Returns y (B,H,P) and, with
     state_f32, the dequantized new state."""
+    if not state_f32 and y_dtype in _YCODE and _plain(x):
+        raw = _raw_stream(stream)
+        r = None if raw is None else _native.decode(
+            x, dt, A, Bq, Cq, B_scale, C_scale, xs_scale, state_scale, cb_scale, state_q, D, corr,
+            int(dt_softplus), int(decay_shift), int(shift_round), y, _YCODE[y_dtype], raw)
+        if r is not None:
+            if r[0] != OK:
+                _check(r[0], "ssdi8_decode_step")
+            return {"y": r[1] if y is None else y}
     _need(x, "x")
     B, H, P = x.shape
     _need(Bq, "Bq", torch.int8)
@@ -586,8 +648,7 @@ class SSDi8Layer:
         out = self._run(x, dt, B, C, y=y, taps=taps, final_state=final_state,
                         stage_events=stage_events, path=path, quantize_in_bmm=quantize_in_bmm,
                         stream=stream)
-        capturing = torch.cuda.is_current_stream_capturing()
-        if check and not capturing:
+        if check and not torch.cuda.is_current_stream_capturing():
             n = self.hand_off_timeouts()
             if n:
                 raise RuntimeError(f"ssdi8_ssd_chunk_scan: {n} single-pass hand-off wait(s) ran "

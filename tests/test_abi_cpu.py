@@ -441,3 +441,27 @@ def test_traffic_source_hash_ignores_comments_only():
     assert bench._code_only(code) == bench._code_only("int f() {  return 1; }\n\nint g;")
     assert bench._code_only(code) != bench._code_only("int f() { return 2; }\nint g;")
     assert bench.kernel_source_sha256("single_pass") is not None
+
+
+def test_single_pass_selection_few_chunks(ssdi8):
+    """One chunk has no hand-off and four chunks a short chain: the single pass at any number of
+    sequences; more chunks from 64 sequences on."""
+    import torch
+    use = lambda *d: ssdi8.uses_single_pass(ssdi8.dims(*d), torch.float16)
+    assert use(1, 256, 1, 1) and use(1, 256, 512, 1)
+    assert use(1, 1024, 8, 1) and use(1, 1024, 64, 1)
+    assert not use(1, 1280, 24, 1) and not use(1, 1280, 63, 1)
+    assert use(1, 1280, 64, 1) and use(2, 4096, 32, 1)
+
+
+def test_native_marshalling_leaves_the_errors_to_python(ssdi8):
+    """Arguments that are not plain device tensors take the general form, with its errors."""
+    import torch
+    with pytest.raises(ValueError, match="src must be a device tensor"):
+        ssdi8.quantize_act(torch.zeros(1, 1, 1, 128))
+    with pytest.raises(ValueError, match="x must be a device tensor"):
+        ssdi8.ssd_chunk_scan(torch.zeros(1, 256, 1, 64), *[None] * 9)
+    assert ssdi8._native.quantize(torch.zeros(1, 1, 1, 128), 1, None, None, 0) is None
+    assert ssdi8._native.scan(*[None] * 26) is None
+    assert ssdi8._native.decode(*[None] * 19) is None
+    assert ssdi8._native.scan() is None

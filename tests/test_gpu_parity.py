@@ -493,3 +493,63 @@ def test_quantize_fp16_row_kernels(torch, ssdi8, shape, gran):
     inv = (np.float32(1) / step).astype(np.float32)
     ref = np.clip(np.rint(src.astype(np.float32) * inv), -127, 127).astype(np.int8)
     assert_equal(q.cpu().numpy(), ref, "codes")
+
+
+def test_native_marshalling_forms(torch, ssdi8):
+    """The native marshalling and the general form (taken with a tap) agree, the caller's tensors
+    come back as they are, and what either refuses raises the same error."""
+    src = torch.randn(2, 3, 4, 128, device="cuda").half()
+    out = torch.empty(src.shape, dtype=torch.int8, device="cuda")
+    step = torch.rand(4, device="cuda") + 0.01
+    q, s = ssdi8.quantize_act(src, "group", step, out=out)
+    assert q is out and s is step
+    for bad, msg in ((dict(scale=step[:3]), "scale must have 4"),
+                     (dict(scale=step.half()), "scale must be"),
+                     (dict(scale=step, out=out[:1]), "out must have shape")):
+        with pytest.raises(ValueError, match=msg):
+            ssdi8.quantize_act(src, "group", **bad)
+    with pytest.raises(ValueError, match="contiguous"):
+        ssdi8.quantize_act(src.transpose(1, 2), "group", step)
+    H, L = 3, 512
+    o = lambda *sh: torch.full(sh, 0.02, device="cuda")
+    x, dt = torch.randn(1, L, H, 64, device="cuda").half(), torch.randn(1, L, H, device="cuda") - 2
+    Bq, Cq = (torch.randint(-127, 128, (1, L, 1, 128), dtype=torch.int8, device="cuda")
+              for _ in range(2))
+    args = (x, dt, -o(H), Bq, Cq, o(1), o(1), o(H, 64), o(H, 64), o(1))
+    y = torch.empty_like(x)
+    a = ssdi8.ssd_chunk_scan(*args, y=y, path="separate")
+    b = ssdi8.ssd_chunk_scan(*args, path="separate", taps=("decay_q",))
+    assert a["y"] is y and set(a) == {"y", "final_state_q", "final_state"}
+    for k in a:
+        assert torch.equal(a[k], b[k]), k
+    f = ssdi8.ssd_chunk_scan(*args, y_dtype=torch.float32, final_state=False)
+    assert set(f) == {"y"} and f["y"].dtype == torch.float32
+    with pytest.raises(ValueError, match="A must have shape"):
+        ssdi8.ssd_chunk_scan(x, dt, o(H + 1), *args[3:])
+    with pytest.raises(ssdi8.SSDi8Error):
+        ssdi8.ssd_chunk_scan(*args, decay_shift=0)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    c = ssdi8.ssd_chunk_scan(*args, path="separate", stream=stream)
+    stream.synchronize()
+    assert torch.equal(c["y"], a["y"])
+
+
+@pytest.mark.parametrize("H,nc", [(1, 1), (24, 1), (3, 4), (64, 5)])
+def test_single_pass_few_chunks(torch, ssdi8, H, nc):
+    """The sizes the automatic choice gives to the single pass with few chunks: identical to the
+    separate kernels, no wait runs out."""
+    torch.manual_seed(H + nc)
+    L = 256 * nc
+    o = lambda *sh: torch.full(sh, 0.02, device="cuda")
+    x, dt = torch.randn(1, L, H, 64, device="cuda").half(), torch.randn(1, L, H, device="cuda") - 2
+    A = -torch.exp(torch.rand(H, device="cuda") * 4 - 4)
+    B, C = (torch.randn(1, L, 1, 128, device="cuda").half() for _ in range(2))
+    to = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    assert ssdi8.uses_single_pass(ssdi8.dims(1, L, H, 1), torch.float16)
+    run = lambda path: ssdi8.ssd_chunk_scan(x, dt, A, None, None, o(1), o(1), o(H, 64), o(H, 64),
+                                            o(1), B=B, C=C, path=path, hand_off_timeouts=to)
+    a, b = run("auto"), run("separate")
+    assert int(to) == 0
+    for k in ("y", "final_state_q", "final_state"):
+        assert torch.equal(a[k], b[k]), k
