@@ -809,7 +809,7 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
     const float er = jt ? __expf((float)s_r[jt - 1]) : 1.0f;
     const bool tap_y1 = !kFused && y1_tap;   // the single pass has no Y1 tap
     const bool need_y1 = tap_y1 || __builtin_amdgcn_readfirstlane((int)(er != 0.0f)) != 0;
-    v16i yi0 = {}, yi1 = {};
+    v16i yi0, yi1;
     if (need_y1) {
       // the P_in fragments are the same for both j-blocks; an opaque offset makes each call
       // load them again (from L2) instead of holding 32 registers across the other block
@@ -821,10 +821,23 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
         b0[ks] = __builtin_bit_cast(v4i, buf_load16(prs, lofs, 1024 * ks));
         b1[ks] = __builtin_bit_cast(v4i, buf_load16(prs, lofs, p1row + 1024 * ks));
       }
+      yi0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(b0[0], a[0], (v16i){}, 0, 0, 0);
+      yi1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(b1[0], a[0], (v16i){}, 0, 0, 0);
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
+      for (int ks = 1; ks < 4; ++ks) {
         yi0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(b0[ks], a[ks], yi0, 0, 0, 0);
         yi1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(b1[ks], a[ks], yi1, 0, 0, 0);
+      }
+    } else {
+      // zeros the compiler does not share with the products above, which start from an inline 0
+      // (shared, the 32 moves ran in every row block)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        int z0, z1;
+        asm volatile("v_mov_b32 %0, 0" : "=v"(z0));
+        asm volatile("v_mov_b32 %0, 0" : "=v"(z1));
+        yi0[r] = z0;
+        yi1[r] = z1;
       }
     }
     // -- epilogue of token row jrow: y = Y1 a_C exp(cs_j) a_S[p] + (y_diag + D x + corr[p])

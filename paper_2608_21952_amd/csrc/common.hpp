@@ -151,6 +151,21 @@ __device__ __forceinline__ uint32_t pack_lo4(uint32_t w0, uint32_t w1, uint32_t 
   return lo | (hi << 16);
 }
 
+// fma with a constant as addend or multiplicand, the constant in scalar registers: left to itself the
+// compiler takes the two-operand form, whose addend is a vector register, and spends a vector move
+// per 32 bits of every constant (about 100 per wave of the single pass, a twentieth of its vector
+// work).  The same operation and rounding.
+__device__ __forceinline__ double fma_add_const(double a, double b, double c) {
+  double d;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+  return d;
+}
+__device__ __forceinline__ double fma_mul_const(double a, double b, double c) {
+  double d;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "s"(b), "v"(c));
+  return d;
+}
+
 // softplus in fp64 with the usual threshold (log1p(exp(v)) for v <= 20, v above), rounded once
 // to fp32.  On [-40, 20] a short fp64 evaluation (relative error below 2^-50) is rounded where it
 // lies at least 2^-44 (relative) from an fp32 rounding boundary, so it rounds as the exact value
@@ -171,18 +186,17 @@ __device__ __forceinline__ float softplus_f32(float v) {
     constexpr double kLog2e = 1.4426950408889634;
     const double x = -__builtin_fabs(d);
     const double k = __builtin_rint(x * kLog2e);
-    double r = __builtin_fma(-k, kLn2Hi, x);
-    r = __builtin_fma(-k, kLn2Lo, r);
-    double p = 1.0 / 479001600.0;                            // 1/12!
-    p = __builtin_fma(p, r, 1.0 / 39916800.0);
-    p = __builtin_fma(p, r, 1.0 / 3628800.0);
-    p = __builtin_fma(p, r, 1.0 / 362880.0);
-    p = __builtin_fma(p, r, 1.0 / 40320.0);
-    p = __builtin_fma(p, r, 1.0 / 5040.0);
-    p = __builtin_fma(p, r, 1.0 / 720.0);
-    p = __builtin_fma(p, r, 1.0 / 120.0);
-    p = __builtin_fma(p, r, 1.0 / 24.0);
-    p = __builtin_fma(p, r, 1.0 / 6.0);
+    double r = fma_mul_const(-k, kLn2Hi, x);
+    r = fma_mul_const(-k, kLn2Lo, r);
+    double p = fma_add_const(1.0 / 479001600.0, r, 1.0 / 39916800.0);   // 1/12!, 1/11!, ...
+    p = fma_add_const(p, r, 1.0 / 3628800.0);
+    p = fma_add_const(p, r, 1.0 / 362880.0);
+    p = fma_add_const(p, r, 1.0 / 40320.0);
+    p = fma_add_const(p, r, 1.0 / 5040.0);
+    p = fma_add_const(p, r, 1.0 / 720.0);
+    p = fma_add_const(p, r, 1.0 / 120.0);
+    p = fma_add_const(p, r, 1.0 / 24.0);
+    p = fma_add_const(p, r, 1.0 / 6.0);
     p = __builtin_fma(p, r, 0.5);
     p = __builtin_fma(p, r, 1.0);
     p = __builtin_fma(p, r, 1.0);
@@ -198,15 +212,14 @@ __device__ __forceinline__ float softplus_f32(float v) {
     const double s0 = f * q;
     const double s = __builtin_fma(__builtin_fma(-den, s0, f), q, s0);
     const double t = s * s;
-    double P = 2.0 / 19.0;
-    P = __builtin_fma(P, t, 2.0 / 17.0);
-    P = __builtin_fma(P, t, 2.0 / 15.0);
-    P = __builtin_fma(P, t, 2.0 / 13.0);
-    P = __builtin_fma(P, t, 2.0 / 11.0);
-    P = __builtin_fma(P, t, 2.0 / 9.0);
-    P = __builtin_fma(P, t, 2.0 / 7.0);
-    P = __builtin_fma(P, t, 2.0 / 5.0);
-    P = __builtin_fma(P, t, 2.0 / 3.0);
+    double P = fma_add_const(2.0 / 19.0, t, 2.0 / 17.0);
+    P = fma_add_const(P, t, 2.0 / 15.0);
+    P = fma_add_const(P, t, 2.0 / 13.0);
+    P = fma_add_const(P, t, 2.0 / 11.0);
+    P = fma_add_const(P, t, 2.0 / 9.0);
+    P = fma_add_const(P, t, 2.0 / 7.0);
+    P = fma_add_const(P, t, 2.0 / 5.0);
+    P = fma_add_const(P, t, 2.0 / 3.0);
     const double corr = __builtin_fma(c, __builtin_amdgcn_rcp(u), big ? kLn2Lo : 0.0);
     const double lo = __builtin_fma(s, t * P, corr);
     const double l1p = (big ? kLn2Hi : 0.0) + (2.0 * s + lo);
