@@ -106,7 +106,8 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
     float cr[kP];
     double r[8];         // r_t: cs at the last token of block t
     double scan[kScanScratch];
-    int misc[4];         // single pass: ticket, q_d, look-back anchor
+    int misc[4];         // single pass: ticket, q_d, look-back anchor at the first look and after
+                         // the wait
     int lq[kLook];       // single pass: Q(Decay) of chunks c-1, c-2, ... (flag words' low half)
     // x^T [p][i] fp16: the ChunkScan2 MFMA operand and, for fp16 x, the D skip operand; then
     // the stage of the fp16 output (256 rows of 128 bytes).  16-byte aligned whatever the
@@ -553,11 +554,14 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
             }
             found = 0;
           }
-          if (lane == 0) sm.misc[2] = found;
+          // a word of its own: no barrier separates an early chunk's first look from here, so a
+          // wave may not have read the first look's anchor yet (it would take this one for it,
+          // and skip the barriers the other waves wait at)
+          if (lane == 0) sm.misc[3] = found;
           if (lane < kLook) sm.lq[lane] = (int)(f & 0xffffu);
         }
         __syncthreads();
-        l = __builtin_amdgcn_readfirstlane(sm.misc[2]);
+        l = __builtin_amdgcn_readfirstlane(sm.misc[3]);
       }
       quiet = early && l == 0;
       // P_in[c-l] (published by the anchor chunk c-1-l) and the S_q of chunks c-l .. c-1, all
