@@ -17,7 +17,13 @@
 // (exp(cs_j - r_{J-1}) exp(r_{J-1} - cs_i)) when its span r_{J-1} - r_J is small enough for the
 // second factor to stay finite; otherwise it evaluates exp per element.
 //
-// Work split: wave w owns the j-blocks {w, 7-w} (1+w + 8-w = 9 causal block pairs per wave).
+// Work split: wave w owns the j-blocks {w, 7-w} (1+w + 8-w = 9 causal block pairs per wave).  Scan1
+// of both comes first, from one load of P_in (it was loaded per block: 64 instead of 32 KB per
+// workgroup through a texture path that is busy 54-87 % of the time), and its scaled result, with
+// the skip and correction terms, seeds the Scan2 accumulators.  Against Scan2 first and the terms
+// added after it: 2.7B-shaped layer 130.6 -> 125.6 us, 8B-shaped 230.4 -> 223.3 us, 64K-token 564.6
+// -> 551.3 us, 130M-shaped 56.5 -> 56.1 us (whole layers).  Requesting the C_q fragments before the
+// hand-off: +-1 %, not kept.
 // Strong decay removes work exactly: leading off-diagonal blocks whose fp16 weights all round to
 // zero are not formed, and Scan1 is not run for a j-block whose factor exp(cs_j) is zero in fp32.
 // x is staged once in LDS as x^T [p][i] (fp16, tokens contiguous = the Scan2 MFMA K-slice); the
@@ -27,7 +33,10 @@
 // let four workgroups share a CU.
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "common.hpp"
+#include "fp16_rows.hpp"
 #include "frag.hpp"
 #include "launch.hpp"
 
@@ -641,47 +650,63 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
   const __amdgpu_buffer_rsrc_t cbrs = buffer_rsrc(cbq + cg * (size_t)frag::kCbChunkBytes);
   const __amdgpu_buffer_rsrc_t cqrs = buffer_rsrc(cq_frag + cg * (size_t)kQ * kN);
   const float Dh = Dv ? Dv[h] : 0.0f;
-  // packed fp16 output of the two j-blocks (8 runs of 4 channels each), staged after the loop
-  uint2 y_first[8], y_second[8];
+  // Scan1 of both row blocks of this wave: Y1^T = P_in . C_q^T, int8 MFMA over n, the P_in
+  // fragments (the same for both) loaded once.  Its term is Y1 a_C exp(cs_j) a_S[p]; when exp(r_{J-1})
+  // is zero in fp32 every factor exp(cs_j) of the block is a zero product and Y1 is not needed (unless
+  // it is tapped); r only falls, so block jtb never needs it without block jta.
+  const int jta = wv, jtb = 7 - wv;
+  auto exp_r = [&](int jt) { return jt ? __expf((float)s_r[jt - 1]) : 1.0f; };   // exp(r_{J-1})
+  const bool tap_y1 = !kFused && y1_tap;   // the single pass has no Y1 tap
 
-  // One j-block of 32 tokens: Scan1, Scan2 and the epilogue; fp16 output packed into yo.
-  auto jblock = [&](int jt, uint2 (&yo)[8]) {
-    // keeps the per-channel epilogue tables of the two calls from being loaded once and held
-    // across both (64 registers), and their addresses from being computed ahead of the call
+  // The rest of a row block on its Y1: y = Y1 a_C exp(cs_j) a_S[p] + D x + corr[p], then Scan2 on top.
+  auto row_block = [&](int jt, bool need, const v16i& yi0, const v16i& yi1, v16f& y0, v16f& y1) {
+    // keeps the per-channel tables of the two calls from being loaded once and held across both
+    // (64 registers), and their addresses from being computed ahead of the call
     asm volatile("" : "+s"(jt) :: "memory");
     const int jrow = jt * 32 + pc;
-    // the C step of this row, for the epilogue (requested first: its wait then drains nothing)
+    // the C step of this row (requested first: its wait then drains nothing)
     const float ac = c_per_token ? C_scale[(tok0 + jrow) * G + g] : C_scale[g];
     const float csrj = s_csr[jrow];
     const float ej = __expf(csrj);                         // exp(cs_j - r_{J-1}), in (0, 1]
     const size_t orow = (tok0 + jrow) * HP + (size_t)h * kP;
-    // -- the Scan2 accumulators start from D x + corr[p] (the skip and correction terms)
-    v16f yd0, yd1;
+    // a_C(j) exp(cs_j) = a_C(j) exp(cs_j - r_{J-1}) exp(r_{J-1})
+    const float eo = ac * ej * exp_r(jt);
+    auto seed = [&](auto with_y1) {
 #pragma unroll
-    for (int pt = 0; pt < 2; ++pt) {
+      for (int pt = 0; pt < 2; ++pt) {
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int pb = pt * 32 + 8 * g4 + 4 * half;
-        const float4 cr4 = *reinterpret_cast<const float4*>(s_cr + pb);
-        const float crv[4] = {cr4.x, cr4.y, cr4.z, cr4.w};
-        float xv[4];
-        if constexpr (sizeof(XT) == 2) {
+        for (int g4 = 0; g4 < 4; ++g4) {
+          const int pb = pt * 32 + 8 * g4 + 4 * half;
+          const float4 cr4 = *reinterpret_cast<const float4*>(s_cr + pb);
+          const float crv[4] = {cr4.x, cr4.y, cr4.z, cr4.w};
+          float xv[4];
+          if constexpr (sizeof(XT) == 2) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            xv[q] = (float)*reinterpret_cast<const _Float16*>(s_xT + (pb + q) * kXTS + jrow * 2);
-        } else {
-          const float4 xf = *reinterpret_cast<const float4*>(x + orow + pb);
-          xv[0] = xf.x; xv[1] = xf.y; xv[2] = xf.z; xv[3] = xf.w;
-        }
+            for (int q = 0; q < 4; ++q)
+              xv[q] = (float)*reinterpret_cast<const _Float16*>(s_xT + (pb + q) * kXTS + jrow * 2);
+          } else {
+            const float4 xf = *reinterpret_cast<const float4*>(x + orow + pb);
+            xv[0] = xf.x; xv[1] = xf.y; xv[2] = xf.z; xv[3] = xf.w;
+          }
+          float asv[4] = {};
+          if constexpr (decltype(with_y1)::value) {
+            const float4 as4 = *reinterpret_cast<const float4*>(s_aS + pb);
+            asv[0] = as4.x; asv[1] = as4.y; asv[2] = as4.z; asv[3] = as4.w;
+          }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float v0 = __builtin_fmaf(Dh, xv[q], crv[q]);
-          if (pt) yd1[4 * g4 + q] = v0;
-          else yd0[4 * g4 + q] = v0;
+          for (int q = 0; q < 4; ++q) {
+            const int r = 4 * g4 + q;
+            float v = __builtin_fmaf(Dh, xv[q], crv[q]);
+            if constexpr (decltype(with_y1)::value)
+              v = __builtin_fmaf((float)(pt ? yi1[r] : yi0[r]) * eo, asv[q], v);
+            if (pt) y1[r] = v;
+            else y0[r] = v;
+          }
         }
       }
-    }
-    v4i a[4], b0[4], b1[4];   // ChunkScan1 operands
+    };
+    if (need) seed(std::true_type{});
+    else seed(std::false_type{});
     // -- Scan2: y_diag^T = x^T . W^T, fp16 MFMA over the causal source tokens i; CB_q of
     //    block it+1 is prefetched while block it is built
     {
@@ -712,8 +737,8 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
         }
         const v8h xa0 = *reinterpret_cast<const v8h*>(s_xT + pc * kXTS + i0 * 2);
         const v8h xa1 = *reinterpret_cast<const v8h*>(s_xT + (32 + pc) * kXTS + i0 * 2);
-        yd0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa0, wf, yd0, 0, 0, 0);
-        yd1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa1, wf, yd1, 0, 0, 0);
+        y0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa0, wf, y0, 0, 0, 0);
+        y1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa1, wf, y1, 0, 0, 0);
       };
       // int8 weight e of a K-slice as the unsigned byte q + 128
       auto qbyte = [](uint32_t ub0, uint32_t ub1, int e) {
@@ -772,14 +797,6 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
       }
       const int js = nb % 3;
       const uint4 cur = js == 0 ? r0 : (js == 1 ? r1 : r2);
-      // the C_q fragments of ChunkScan1, in flight during the diagonal block
-      {
-        const uint32_t crow = jt * (kN / 32) * 1024;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-          a[ks] = __builtin_bit_cast(v4i, buf_load16(cqrs, lane16, crow + 1024 * ks));
-        __builtin_amdgcn_sched_barrier(0);
-      }
       // diagonal block it = jt: its entries i > j hold the code of zero, whose weight
       // fma(128, d, -128 d) is exactly +0, so no mask is needed
 #pragma unroll
@@ -807,122 +824,80 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
         mfma_block(wv, i0);
       }
     }
-    // -- Scan1: Y1^T = P_in . C_q^T, int8 MFMA over n.  Its term is Y1 a_C exp(cs_j) a_S[p];
-    //    when exp(r_{J-1}) is zero in fp32 every factor exp(cs_j) of the block is a zero
-    //    product and Y1 is not needed (unless it is tapped)
-    const float er = jt ? __expf((float)s_r[jt - 1]) : 1.0f;
-    const bool tap_y1 = !kFused && y1_tap;   // the single pass has no Y1 tap
-    const bool need_y1 = tap_y1 || __builtin_amdgcn_readfirstlane((int)(er != 0.0f)) != 0;
-    v16i yi0, yi1;
-    if (need_y1) {
-      // the P_in fragments are the same for both j-blocks; an opaque offset makes each call
-      // load them again (from L2) instead of holding 32 registers across the other block
-      uint32_t lofs = lane16;
-      asm volatile("" : "+v"(lofs));
-      constexpr uint32_t p1row = (kN / 32) * 1024;
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        b0[ks] = __builtin_bit_cast(v4i, buf_load16(prs, lofs, 1024 * ks));
-        b1[ks] = __builtin_bit_cast(v4i, buf_load16(prs, lofs, p1row + 1024 * ks));
-      }
-      yi0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(b0[0], a[0], (v16i){}, 0, 0, 0);
-      yi1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(b1[0], a[0], (v16i){}, 0, 0, 0);
-#pragma unroll
-      for (int ks = 1; ks < 4; ++ks) {
-        yi0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(b0[ks], a[ks], yi0, 0, 0, 0);
-        yi1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(b1[ks], a[ks], yi1, 0, 0, 0);
-      }
-    } else {
-      // zeros the compiler does not share with the products above, which start from an inline 0
-      // (shared, the 32 moves ran in every row block)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        int z0, z1;
-        asm volatile("v_mov_b32 %0, 0" : "=v"(z0));
-        asm volatile("v_mov_b32 %0, 0" : "=v"(z1));
-        yi0[r] = z0;
-        yi1[r] = z1;
-      }
-    }
-    // -- epilogue of token row jrow: y = Y1 a_C exp(cs_j) a_S[p] + (y_diag + D x + corr[p])
-    // a_C(j) exp(cs_j) = a_C(j) exp(cs_j - r_{J-1}) exp(r_{J-1})
-    const float eo = ac * ej * er;
-#pragma unroll
-    for (int pt = 0; pt < 2; ++pt) {
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int pb = pt * 32 + 8 * g4 + 4 * half;
-        const float4 as4 = *reinterpret_cast<const float4*>(s_aS + pb);
-        const float asv[4] = {as4.x, as4.y, as4.z, as4.w};
-        float v[4];
-        int yi[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int r = 4 * g4 + q;
-          yi[q] = pt ? yi1[r] : yi0[r];
-          const float yd = pt ? yd1[r] : yd0[r];
-          v[q] = __builtin_fmaf((float)yi[q] * eo, asv[q], yd);
-        }
-        if (tap_y1)
-          *reinterpret_cast<int4*>(y1_tap + orow + pb) = make_int4(yi[0], yi[1], yi[2], yi[3]);
-        if constexpr (sizeof(YT) == 4) {
-          *reinterpret_cast<float4*>(y + orow + pb) = make_float4(v[0], v[1], v[2], v[3]);
-        } else {
-          typedef float f2_t __attribute__((ext_vector_type(2)));
-          typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
-          const h2_t h01 = __builtin_convertvector((f2_t){v[0], v[1]}, h2_t);
-          const h2_t h23 = __builtin_convertvector((f2_t){v[2], v[3]}, h2_t);
-          uint2 o = make_uint2(__builtin_bit_cast(uint32_t, h01), __builtin_bit_cast(uint32_t, h23));
-          // pinned here: otherwise the arithmetic sinks to the stage writes after the other
-          // j-block and keeps this block's accumulators and tables alive across it
-          asm volatile("" : "+v"(o.x), "+v"(o.y));
-          yo[4 * pt + g4] = o;
-        }
-      }
-    }
   };
   if constexpr (kFused) hand_off();
-  jblock(wv, y_first);
-  jblock(7 - wv, y_second);
+  const bool need_a =
+      tap_y1 || __builtin_amdgcn_readfirstlane((int)(exp_r(jta) != 0.0f)) != 0;
+  const bool need_b =
+      tap_y1 || __builtin_amdgcn_readfirstlane((int)(exp_r(jtb) != 0.0f)) != 0;
+  v16i ia0, ia1, ib0, ib1;
+  {
+    const uint32_t ca = jta * (kN / 32) * 1024, cb = jtb * (kN / 32) * 1024;
+    constexpr uint32_t p1row = (kN / 32) * 1024;
+    auto frag_of = [&](__amdgpu_buffer_rsrc_t r, uint32_t o) {
+      return __builtin_bit_cast(v4i, buf_load16(r, lane16, o));
+    };
+    if (need_b) {
+#pragma unroll
+      for (int ks = 0; ks < kN / 32; ++ks) {
+        const v4i p0 = frag_of(prs, 1024 * ks), p1 = frag_of(prs, p1row + 1024 * ks);
+        const v4i fa = frag_of(cqrs, ca + 1024 * ks), fb = frag_of(cqrs, cb + 1024 * ks);
+        ia0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p0, fa, ks ? ia0 : (v16i){}, 0, 0, 0);
+        ia1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p1, fa, ks ? ia1 : (v16i){}, 0, 0, 0);
+        ib0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p0, fb, ks ? ib0 : (v16i){}, 0, 0, 0);
+        ib1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p1, fb, ks ? ib1 : (v16i){}, 0, 0, 0);
+      }
+    } else if (need_a) {
+#pragma unroll
+      for (int ks = 0; ks < kN / 32; ++ks) {
+        const v4i p0 = frag_of(prs, 1024 * ks), p1 = frag_of(prs, p1row + 1024 * ks);
+        const v4i fa = frag_of(cqrs, ca + 1024 * ks);
+        ia0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p0, fa, ks ? ia0 : (v16i){}, 0, 0, 0);
+        ia1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p1, fa, ks ? ia1 : (v16i){}, 0, 0, 0);
+      }
+      asm volatile("" : "=v"(ib0), "=v"(ib1));   // never read
+    } else {
+      asm volatile("" : "=v"(ia0), "=v"(ia1), "=v"(ib0), "=v"(ib1));   // never read
+    }
+  }
+  if (tap_y1) {   // row-major debug copy
+    auto tap = [&](int jt, const v16i& y0, const v16i& y1) {
+      int32_t* row = y1_tap + (tok0 + jt * 32 + pc) * HP + (size_t)h * kP + 4 * half;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const v16i& v = q < 4 ? y0 : y1;
+        const int r = 4 * (q & 3);
+        *reinterpret_cast<int4*>(row + 8 * q) = make_int4(v[r], v[r + 1], v[r + 2], v[r + 3]);
+      }
+    };
+    tap(jta, ia0, ia1);
+    tap(jtb, ib0, ib1);
+  }
+  v16f ya0, ya1, yb0, yb1;
+  row_block(jta, need_a, ia0, ia1, ya0, ya1);
+  row_block(jtb, need_b, ib0, ib1, yb0, yb1);
 
   if constexpr (sizeof(YT) == 2) {
     // fp16 output leaves through LDS as whole 128-byte token rows.  The stage reuses the x^T
     // bytes once every wave is done with them: row j at 128 j, its 16-byte column chunk k at
     // slot k ^ (j & 7) (conflict-free 8-byte writes by token and 16-byte reads by row).
     __syncthreads();
-    uint8_t* s_y = s_xT;
-    {
-      // this lane's rows are 32 jt + pc, so j & 7 = pc & 7 for both j-blocks
-      const uint32_t jx = pc & 7;
-      uint8_t* r0 = s_y + (wv * 32 + pc) * 128 + 8 * half;
-      uint8_t* r1 = s_y + ((7 - wv) * 32 + pc) * 128 + 8 * half;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const uint32_t so = (k ^ jx) * 16;
-        *reinterpret_cast<uint2*>(r0 + so) = y_first[k];
-        *reinterpret_cast<uint2*>(r1 + so) = y_second[k];
-      }
-    }
+    fp16::stage_rows_f16(s_xT, jta, lane, ya0, ya1);
+    fp16::stage_rows_f16(s_xT, jtb, lane, yb0, yb1);
     __syncthreads();
-    {
-      // thread: token rows 32 k + t / 8 (k = 0..7), 16-byte column t % 8; (t / 8) & 7 is the
-      // row's swizzle for every k
-      const int jt8 = t >> 3, col = t & 7;
-      const uint8_t* src = s_y + jt8 * 128 + ((col ^ (jt8 & 7)) * 16);
-      const __amdgpu_buffer_rsrc_t yrs = buffer_rsrc(y + tok0 * HP + (size_t)h * kP);
-      const uint32_t yo = (uint32_t)(jt8 * HP * 2 + col * 16);
-      if (fs.stream) {
-#pragma unroll
-        for (int k = 0; k < (kQ * kP * 2) / (16 * 256); ++k)
-          buf_store16<kPolicyNT>(*reinterpret_cast<const uint4*>(src + k * 32 * 128), yrs, yo,
-                                 (uint32_t)(k * 32 * HP * 2));
-      } else {
-#pragma unroll
-        for (int k = 0; k < (kQ * kP * 2) / (16 * 256); ++k)
-          buf_store16(*reinterpret_cast<const uint4*>(src + k * 32 * 128), yrs, yo,
-                      (uint32_t)(k * 32 * HP * 2));
-      }
-    }
+    fp16::rows_out<128, 256>(s_xT, buffer_rsrc(y + tok0 * HP + (size_t)h * kP), t, HP, 0,
+                             fs.stream);
+  } else {
+    // fp32: 128 rows at a time
+    const __amdgpu_buffer_rsrc_t yrs = buffer_rsrc(y + tok0 * HP + (size_t)h * kP);
+    __syncthreads();
+    fp16::stage_rows_f32(s_xT, jta, lane, ya0, ya1);
+    __syncthreads();
+    fp16::rows_out<256, 256>(s_xT, yrs, t, HP, 0, fs.stream);
+    __syncthreads();
+    fp16::stage_rows_f32(s_xT, jtb - 4, lane, yb0, yb1);
+    __syncthreads();
+    fp16::rows_out<256, 256>(s_xT, yrs, t, HP, 128, fs.stream);
   }
 }
 
