@@ -132,8 +132,9 @@ struct CalibPlan {
 };
 
 // Calibration workspace: the FP16 layer's and the INT8 layer's workspaces, the quantized B and C,
-// the two fp32 outputs Y_fp and Y_q, the fp64 chunk decays, and the absmax words (x: H*P,
-// states: H*P, C.B^T: G).
+// two regions sized for fp32 outputs Y_fp and Y_q, whose channel sums per chunk take a 128th of
+// them, the fp64 chunk decays, and the absmax words (x: H*P, states: H*P).  The regions keep the
+// sizes the workspace has always had, `part` (64 H P doubles) unused among them.
 CalibPlan plan_calib(const ssdi8_dims* d) {
   const size_t B = (size_t)d->batch, L = (size_t)d->seqlen, H = (size_t)d->nheads;
   const size_t P = (size_t)d->headdim, G = (size_t)d->ngroups, N = (size_t)d->dstate;
@@ -150,7 +151,7 @@ CalibPlan plan_calib(const ssdi8_dims* d) {
   p.yq = off;       off = round_up(off + 4 * B * L * H * P, 256);
   p.dec64 = off;    off = round_up(off + 8 * B * H * nc, 256);
   p.amax = off;     off = round_up(off + 4 * (2 * H * P + G), 256);
-  p.part = off;     off = round_up(off + ssdi8::calib_corr_scratch_bytes((int)H), 256);
+  p.part = off;     off = round_up(off + 8 * 64 * H * P, 256);
   p.total = off;
   return p;
 }
@@ -193,6 +194,142 @@ bool single_pass(const ssdi8_dims* d, const ssdi8_scan_args* a) {
   const int64_t nc = d->chunk > 0 ? d->seqlen / d->chunk : 0;
   const int64_t bh = d->batch * d->nheads;
   return nc == 1 || nc == 4 || (bh >= 64 && nc >= 4) || (bh >= 48 && nc >= 32);
+}
+
+// ssdi8_ssd_chunk_scan; with `sums` y is the channel sums of calibration (y_dtype kYSums).
+ssdi8_status run_layer(const ssdi8_dims* d, const ssdi8_scan_args* a, void* stream, bool sums) {
+  ssdi8_status s = check_dims(d);
+  if (s != SSDI8_OK) return s;
+  if (!a) return SSDI8_ERR_NULL;
+  if (a->x_dtype != SSDI8_F32 && a->x_dtype != SSDI8_F16) return SSDI8_ERR_ARG;
+  if (!sums && a->y_dtype != SSDI8_F32 && a->y_dtype != SSDI8_F16) return SSDI8_ERR_ARG;
+  if (a->decay_shift < 1 || a->decay_shift > 14) return SSDI8_ERR_ARG;
+  if (a->path < 0 || a->path > 2) return SSDI8_ERR_ARG;
+  const bool work = d->batch > 0 && d->seqlen > 0;
+  // B, C: quantized (Bq, Cq) or unquantized (B, C with bc_dtype), not both, not a mix
+  const bool quantized = a->Bq || a->Cq;
+  if (quantized && (a->B || a->C)) return SSDI8_ERR_ARG;
+  if (!quantized && (a->B || a->C) && a->bc_dtype != SSDI8_F32 && a->bc_dtype != SSDI8_F16)
+    return SSDI8_ERR_ARG;
+  const void* Bsrc = quantized ? (const void*)a->Bq : a->B;
+  const void* Csrc = quantized ? (const void*)a->Cq : a->C;
+  if (work && (!a->x || !a->dt || !a->A || !Bsrc || !Csrc || !a->B_scale || !a->C_scale ||
+               !a->xs_scale || !a->state_scale || !a->cb_scale || !a->y))
+    return SSDI8_ERR_NULL;
+  if (a->final_state && !a->state_scale) return SSDI8_ERR_NULL;
+  if ((uintptr_t)a->hand_off_timeouts & 3u) return SSDI8_ERR_ALIGN;
+  const void* al[] = {a->x, a->y, a->Bq, a->Cq, a->B, a->C, a->init_state_q, a->final_state_q,
+                      a->final_state, a->xs_q, a->state_i32, a->state_q, a->decay_q,
+                      a->state_in_q, a->cb_i32, a->cb_q, a->scan1_i32, a->dt_post,
+                      a->workspace};
+  for (const void* p : al)
+    if (!aligned16_or_null(p)) return SSDI8_ERR_ALIGN;
+  const Plan plan = plan_workspace(d);
+  if (work && (!a->workspace || a->workspace_bytes < plan.total)) return SSDI8_ERR_WORKSPACE;
+  if (a->stage_events)
+    for (int i = 0; i < 5; ++i)
+      if (!a->stage_events[i]) return SSDI8_ERR_NULL;
+
+  hipStream_t st = (hipStream_t)stream;
+  LayerDims ld;
+  ld.batch = (int)d->batch;
+  ld.seqlen = (int)d->seqlen;
+  ld.nheads = (int)d->nheads;
+  ld.ngroups = (int)d->ngroups;
+  ld.nchunks = (int)(d->seqlen / d->chunk);
+  const int64_t elems = d->headdim * d->dstate;
+
+  if (!work) {
+    // no tokens: the final state is the initial state
+    if (d->batch > 0 && (a->final_state_q || a->final_state)) {
+      hipError_t e = ssdi8::launch_state_pass(d->batch, 0, d->nheads, elems, d->headdim,
+                                              nullptr, nullptr, a->decay_shift, a->shift_round,
+                                              a->init_state_q, nullptr, nullptr,
+                                              a->final_state_q, a->final_state, a->state_scale,
+                                              0, st);
+      if (e != hipSuccess) return SSDI8_ERR_HIP;
+    }
+    return SSDI8_OK;
+  }
+
+  char* ws = static_cast<char*>(a->workspace);
+  int8_t* bqT = reinterpret_cast<int8_t*>(ws + plan.bqT);
+  int8_t* cq = reinterpret_cast<int8_t*>(ws + plan.cq);
+  int8_t* sq = reinterpret_cast<int8_t*>(ws + plan.sq);
+  int8_t* pin = reinterpret_cast<int8_t*>(ws + plan.pin);
+  int8_t* cbq = reinterpret_cast<int8_t*>(ws + plan.cbq);
+  int16_t* qd = a->decay_q ? a->decay_q : reinterpret_cast<int16_t*>(ws + plan.qd);
+
+  // stage events: 0 and 1 are ChunkBMM's own start and end, 3 and 4 the ChunkScan (or single
+  // pass) kernel's; 2 is recorded on the stream after ChunkState (after ChunkBMM on the single
+  // pass), so StatePassing's share runs from it to ChunkScan's start
+  hipEvent_t ev[5] = {};
+  if (a->stage_events)
+    for (int i = 0; i < 5; ++i) ev[i] = static_cast<hipEvent_t>(a->stage_events[i]);
+  auto mark = [&](int i) -> bool {
+    return !a->stage_events || hipEventRecord(ev[i], st) == hipSuccess;
+  };
+  const int y_bytes = sums ? 0 : (a->y_dtype == SSDI8_F16 ? 2 : 4);
+  const bool fused = single_pass(d, a);
+  int* sync = reinterpret_cast<int*>(ws + plan.sync);
+  hipError_t e = ssdi8::launch_chunk_bmm(ld, Csrc, Bsrc, quantized ? -1 : a->bc_dtype,
+                                         a->C_scale, a->c_per_token,
+                                         a->B_scale, a->cb_scale, cbq, a->cb_q, a->cb_i32, bqT,
+                                         cq, fused ? 1 : 0, sync, fused ? (int)plan.nsync : 0,
+                                         a->hand_off_timeouts, st, ev[0], ev[1]);
+  if (e != hipSuccess) return SSDI8_ERR_HIP;
+  if (fused) {
+    if (!mark(2)) return SSDI8_ERR_HIP;
+    ssdi8::FusedState fs;
+    fs.bqT = bqT;
+    fs.sq = sq;
+    fs.B_scale = a->B_scale;
+    fs.xs_scale = a->xs_scale;
+    fs.xs_per_head = a->xs_per_head;
+    fs.shift = a->decay_shift;
+    fs.radd = a->shift_round ? (1 << (a->decay_shift - 1)) : 0;
+    fs.init = a->init_state_q;
+    fs.final_q = a->final_state_q;
+    fs.final_state = a->final_state;
+    fs.sync = sync;
+    fs.timeouts = a->hand_off_timeouts;
+    fs.nbh = ld.batch * ld.nheads;
+    fs.nclass = ssdi8::sync_classes(fs.nbh);
+    fs.spin_limit = 1 << 16;   // polls of ~1 us: a wait gives up after ~65 ms
+    // at most two rounds of workgroups (four per CU): the first loads of every item wait in
+    // full, so they are requested with the ticket for the item dispatch order predicts
+    const int64_t nitems = (int64_t)ld.batch * ld.nchunks * ld.nheads;
+    fs.speculate = nitems <= (int64_t)8 * device_cus() ? 1 : 0;
+    fs.stream = ssdi8::stream_xy(ld, 2, y_bytes);
+    e = ssdi8::launch_chunk_scan_fused(ld, static_cast<const _Float16*>(a->x), a->dt,
+                                       a->dt_softplus, a->A, cq, a->C_scale, a->c_per_token, pin,
+                                       cbq, a->cb_scale, a->state_scale, a->D, a->corr, a->y,
+                                       a->y_dtype, fs, st, ev[3], ev[4]);
+    if (e != hipSuccess) return SSDI8_ERR_HIP;
+    if (a->state_in_q) {
+      e = ssdi8::launch_pin_tap(pin, a->state_in_q, (int64_t)ld.batch * ld.nchunks * ld.nheads,
+                                st);
+      if (e != hipSuccess) return SSDI8_ERR_HIP;
+    }
+    return SSDI8_OK;
+  }
+  e = ssdi8::launch_chunk_state(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, bqT,
+                                a->B_scale, a->xs_scale, a->xs_per_head, a->state_scale,
+                                a->decay_shift, sq, qd, a->xs_q, a->state_q, a->state_i32,
+                                a->dt_post, st);
+  if (e != hipSuccess || !mark(2)) return SSDI8_ERR_HIP;
+  e = ssdi8::launch_state_pass(d->batch, ld.nchunks, d->nheads, elems, d->headdim, sq, qd,
+                               a->decay_shift, a->shift_round, a->init_state_q, pin,
+                               a->state_in_q, a->final_state_q, a->final_state, a->state_scale,
+                               (int)d->dstate, st);
+  if (e != hipSuccess) return SSDI8_ERR_HIP;
+  e = ssdi8::launch_chunk_scan(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, cq,
+                               a->C_scale, a->c_per_token, pin, cbq, a->cb_scale, a->state_scale,
+                               a->D, a->corr, a->y, a->y_dtype, a->scan1_i32,
+                               ssdi8::stream_xy(ld, a->x_dtype == SSDI8_F16 ? 2 : 4, y_bytes),
+                               st, ev[3], ev[4]);
+  if (e != hipSuccess) return SSDI8_ERR_HIP;
+  return SSDI8_OK;
 }
 
 }  // namespace
@@ -273,138 +410,7 @@ size_t ssdi8_ssd_workspace_size(const ssdi8_dims* d) {
 }
 
 ssdi8_status ssdi8_ssd_chunk_scan(const ssdi8_dims* d, const ssdi8_scan_args* a, void* stream) {
-  ssdi8_status s = check_dims(d);
-  if (s != SSDI8_OK) return s;
-  if (!a) return SSDI8_ERR_NULL;
-  if (a->x_dtype != SSDI8_F32 && a->x_dtype != SSDI8_F16) return SSDI8_ERR_ARG;
-  if (a->y_dtype != SSDI8_F32 && a->y_dtype != SSDI8_F16) return SSDI8_ERR_ARG;
-  if (a->decay_shift < 1 || a->decay_shift > 14) return SSDI8_ERR_ARG;
-  if (a->path < 0 || a->path > 2) return SSDI8_ERR_ARG;
-  const bool work = d->batch > 0 && d->seqlen > 0;
-  // B, C: quantized (Bq, Cq) or unquantized (B, C with bc_dtype), not both, not a mix
-  const bool quantized = a->Bq || a->Cq;
-  if (quantized && (a->B || a->C)) return SSDI8_ERR_ARG;
-  if (!quantized && (a->B || a->C) && a->bc_dtype != SSDI8_F32 && a->bc_dtype != SSDI8_F16)
-    return SSDI8_ERR_ARG;
-  const void* Bsrc = quantized ? (const void*)a->Bq : a->B;
-  const void* Csrc = quantized ? (const void*)a->Cq : a->C;
-  if (work && (!a->x || !a->dt || !a->A || !Bsrc || !Csrc || !a->B_scale || !a->C_scale ||
-               !a->xs_scale || !a->state_scale || !a->cb_scale || !a->y))
-    return SSDI8_ERR_NULL;
-  if (a->final_state && !a->state_scale) return SSDI8_ERR_NULL;
-  if ((uintptr_t)a->hand_off_timeouts & 3u) return SSDI8_ERR_ALIGN;
-  const void* al[] = {a->x, a->y, a->Bq, a->Cq, a->B, a->C, a->init_state_q, a->final_state_q,
-                      a->final_state, a->xs_q, a->state_i32, a->state_q, a->decay_q,
-                      a->state_in_q, a->cb_i32, a->cb_q, a->scan1_i32, a->dt_post,
-                      a->workspace};
-  for (const void* p : al)
-    if (!aligned16_or_null(p)) return SSDI8_ERR_ALIGN;
-  const Plan plan = plan_workspace(d);
-  if (work && (!a->workspace || a->workspace_bytes < plan.total)) return SSDI8_ERR_WORKSPACE;
-  if (a->stage_events)
-    for (int i = 0; i < 5; ++i)
-      if (!a->stage_events[i]) return SSDI8_ERR_NULL;
-
-  hipStream_t st = (hipStream_t)stream;
-  LayerDims ld;
-  ld.batch = (int)d->batch;
-  ld.seqlen = (int)d->seqlen;
-  ld.nheads = (int)d->nheads;
-  ld.ngroups = (int)d->ngroups;
-  ld.nchunks = (int)(d->seqlen / d->chunk);
-  const int64_t elems = d->headdim * d->dstate;
-
-  if (!work) {
-    // no tokens: the final state is the initial state
-    if (d->batch > 0 && (a->final_state_q || a->final_state)) {
-      hipError_t e = ssdi8::launch_state_pass(d->batch, 0, d->nheads, elems, d->headdim,
-                                              nullptr, nullptr, a->decay_shift, a->shift_round,
-                                              a->init_state_q, nullptr, nullptr,
-                                              a->final_state_q, a->final_state, a->state_scale,
-                                              0, st);
-      if (e != hipSuccess) return SSDI8_ERR_HIP;
-    }
-    return SSDI8_OK;
-  }
-
-  char* ws = static_cast<char*>(a->workspace);
-  int8_t* bqT = reinterpret_cast<int8_t*>(ws + plan.bqT);
-  int8_t* cq = reinterpret_cast<int8_t*>(ws + plan.cq);
-  int8_t* sq = reinterpret_cast<int8_t*>(ws + plan.sq);
-  int8_t* pin = reinterpret_cast<int8_t*>(ws + plan.pin);
-  int8_t* cbq = reinterpret_cast<int8_t*>(ws + plan.cbq);
-  int16_t* qd = a->decay_q ? a->decay_q : reinterpret_cast<int16_t*>(ws + plan.qd);
-
-  // stage events: 0 and 1 are ChunkBMM's own start and end, 3 and 4 the ChunkScan (or single
-  // pass) kernel's; 2 is recorded on the stream after ChunkState (after ChunkBMM on the single
-  // pass), so StatePassing's share runs from it to ChunkScan's start
-  hipEvent_t ev[5] = {};
-  if (a->stage_events)
-    for (int i = 0; i < 5; ++i) ev[i] = static_cast<hipEvent_t>(a->stage_events[i]);
-  auto mark = [&](int i) -> bool {
-    return !a->stage_events || hipEventRecord(ev[i], st) == hipSuccess;
-  };
-  const bool fused = single_pass(d, a);
-  int* sync = reinterpret_cast<int*>(ws + plan.sync);
-  hipError_t e = ssdi8::launch_chunk_bmm(ld, Csrc, Bsrc, quantized ? -1 : a->bc_dtype,
-                                         a->C_scale, a->c_per_token,
-                                         a->B_scale, a->cb_scale, cbq, a->cb_q, a->cb_i32, bqT,
-                                         cq, fused ? 1 : 0, sync, fused ? (int)plan.nsync : 0,
-                                         a->hand_off_timeouts, st, ev[0], ev[1]);
-  if (e != hipSuccess) return SSDI8_ERR_HIP;
-  if (fused) {
-    if (!mark(2)) return SSDI8_ERR_HIP;
-    ssdi8::FusedState fs;
-    fs.bqT = bqT;
-    fs.sq = sq;
-    fs.B_scale = a->B_scale;
-    fs.xs_scale = a->xs_scale;
-    fs.xs_per_head = a->xs_per_head;
-    fs.shift = a->decay_shift;
-    fs.radd = a->shift_round ? (1 << (a->decay_shift - 1)) : 0;
-    fs.init = a->init_state_q;
-    fs.final_q = a->final_state_q;
-    fs.final_state = a->final_state;
-    fs.sync = sync;
-    fs.timeouts = a->hand_off_timeouts;
-    fs.nbh = ld.batch * ld.nheads;
-    fs.nclass = ssdi8::sync_classes(fs.nbh);
-    fs.spin_limit = 1 << 16;   // polls of ~1 us: a wait gives up after ~65 ms
-    // at most two rounds of workgroups (four per CU): the first loads of every item wait in
-    // full, so they are requested with the ticket for the item dispatch order predicts
-    const int64_t nitems = (int64_t)ld.batch * ld.nchunks * ld.nheads;
-    fs.speculate = nitems <= (int64_t)8 * device_cus() ? 1 : 0;
-    fs.stream = ssdi8::stream_xy(ld, 2, a->y_dtype == SSDI8_F16 ? 2 : 4);
-    e = ssdi8::launch_chunk_scan_fused(ld, static_cast<const _Float16*>(a->x), a->dt,
-                                       a->dt_softplus, a->A, cq, a->C_scale, a->c_per_token, pin,
-                                       cbq, a->cb_scale, a->state_scale, a->D, a->corr, a->y,
-                                       a->y_dtype, fs, st, ev[3], ev[4]);
-    if (e != hipSuccess) return SSDI8_ERR_HIP;
-    if (a->state_in_q) {
-      e = ssdi8::launch_pin_tap(pin, a->state_in_q, (int64_t)ld.batch * ld.nchunks * ld.nheads,
-                                st);
-      if (e != hipSuccess) return SSDI8_ERR_HIP;
-    }
-    return SSDI8_OK;
-  }
-  e = ssdi8::launch_chunk_state(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, bqT,
-                                a->B_scale, a->xs_scale, a->xs_per_head, a->state_scale,
-                                a->decay_shift, sq, qd, a->xs_q, a->state_q, a->state_i32,
-                                a->dt_post, st);
-  if (e != hipSuccess || !mark(2)) return SSDI8_ERR_HIP;
-  e = ssdi8::launch_state_pass(d->batch, ld.nchunks, d->nheads, elems, d->headdim, sq, qd,
-                               a->decay_shift, a->shift_round, a->init_state_q, pin,
-                               a->state_in_q, a->final_state_q, a->final_state, a->state_scale,
-                               (int)d->dstate, st);
-  if (e != hipSuccess) return SSDI8_ERR_HIP;
-  e = ssdi8::launch_chunk_scan(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, cq,
-                               a->C_scale, a->c_per_token, pin, cbq, a->cb_scale, a->state_scale,
-                               a->D, a->corr, a->y, a->y_dtype, a->scan1_i32,
-                               ssdi8::stream_xy(ld, a->x_dtype == SSDI8_F16 ? 2 : 4,
-                                                a->y_dtype == SSDI8_F16 ? 2 : 4),
-                               st, ev[3], ev[4]);
-  if (e != hipSuccess) return SSDI8_ERR_HIP;
-  return SSDI8_OK;
+  return run_layer(d, a, stream, false);
 }
 
 ssdi8_status ssdi8_ssd_chunk_scan_noalloc(const ssdi8_dims* d, const ssdi8_scan_args* a,
@@ -478,7 +484,7 @@ ssdi8_status ssdi8_ssd_chunk_scan_fp16(const ssdi8_dims* d, const ssdi8_fp16_arg
   };
   if (!mark(0)) return SSDI8_ERR_HIP;
   hipError_t e = ssdi8::launch_fp16_bmm(ld, a->C, a->B, a->bc_dtype, cb, bT, c16, cbmax,
-                                          nullptr, st);
+                                          st);
   if (e != hipSuccess || !mark(1)) return SSDI8_ERR_HIP;
   if (fp16_walks(ld)) {
     e = ssdi8::launch_fp16_walk(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, bT,
@@ -545,15 +551,14 @@ ssdi8_status ssdi8_calibrate(const ssdi8_dims* d, const ssdi8_calib_args* a, voi
   char* i8 = ws + plan.i8_base;
   int8_t* Bq = reinterpret_cast<int8_t*>(ws + plan.bq);
   int8_t* Cq = reinterpret_cast<int8_t*>(ws + plan.cq);
-  float* yfp = reinterpret_cast<float*>(ws + plan.yfp);
-  float* yq = reinterpret_cast<float*>(ws + plan.yq);
+  double* sum_fp = reinterpret_cast<double*>(ws + plan.yfp);
+  double* sum_q = reinterpret_cast<double*>(ws + plan.yq);
   double* dec64 = reinterpret_cast<double*>(ws + plan.dec64);
   uint32_t* xs_amax = reinterpret_cast<uint32_t*>(ws + plan.amax);
   uint32_t* s_amax = xs_amax + H * P;
-  uint32_t* cb_amax = s_amax + H * P;
 
   // steps of B and C (dynamic per-group absmax), then the quantities the other steps are taken of
-  hipError_t e = ssdi8::launch_calib_zero(xs_amax, 2 * H * P + G, st);
+  hipError_t e = ssdi8::launch_calib_zero(xs_amax, 2 * H * P, st);
   if (e == hipSuccess)
     e = ssdi8::launch_quantize(a->B, a->bc_dtype, d->batch, d->seqlen, d->ngroups, d->dstate,
                                SSDI8_GRAN_GROUP, a->B_scale, 1, Bq, st);
@@ -561,16 +566,13 @@ ssdi8_status ssdi8_calibrate(const ssdi8_dims* d, const ssdi8_calib_args* a, voi
     e = ssdi8::launch_quantize(a->C, a->bc_dtype, d->batch, d->seqlen, d->ngroups, d->dstate,
                                SSDI8_GRAN_GROUP, a->C_scale, 1, Cq, st);
   if (e == hipSuccess)
-    e = ssdi8::launch_calib_xs(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, xs_amax, st);
+    e = ssdi8::launch_fp16_bmm(ld, a->C, a->B, a->bc_dtype, cb, bT, c16, cbmax, st);
   if (e == hipSuccess)
-    e = ssdi8::launch_fp16_bmm(ld, a->C, a->B, a->bc_dtype, cb, bT, c16, cbmax, cb_amax,
-                                st);
+    e = ssdi8::launch_calib_states(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, bT, xs_amax,
+                                   S, dec64, s_amax, st);
   if (e == hipSuccess)
-    e = ssdi8::launch_calib_states(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, bT, S,
-                                   dec64, s_amax, st);
-  if (e == hipSuccess)
-    e = ssdi8::launch_calib_steps(xs_amax, s_amax, cb_amax, a->xs_scale, a->state_scale,
-                                  a->cb_scale, H, G, a->xs_per_head, st);
+    e = ssdi8::launch_calib_steps(ld, xs_amax, s_amax, cbmax, a->xs_scale, a->state_scale,
+                                  a->cb_scale, a->xs_per_head, st);
   // Y_fp: the FP16 layer (its ChunkBMM outputs are already in place)
   if (e == hipSuccess && fp16_walks(ld)) {
     e = ssdi8::launch_fp16_walk(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, bT, nullptr,
@@ -582,7 +584,7 @@ ssdi8_status ssdi8_calibrate(const ssdi8_dims* d, const ssdi8_calib_args* a, voi
   }
   if (e == hipSuccess)
     e = ssdi8::launch_fp16_scan(ld, a->x, a->x_dtype, a->dt, a->dt_softplus, a->A, c16, pin16,
-                                cb, cbmax, a->D, yfp, SSDI8_F32, st);
+                                cb, cbmax, a->D, sum_fp, ssdi8::kYSums, st);
   // Y_q: the INT8 layer with the new steps and no correction, as ssdi8_ssd_chunk_scan runs it
   if (e != hipSuccess) return SSDI8_ERR_HIP;
   {
@@ -603,16 +605,15 @@ ssdi8_status ssdi8_calibrate(const ssdi8_dims* d, const ssdi8_calib_args* a, voi
     la.cb_scale = a->cb_scale;
     la.decay_shift = a->decay_shift;
     la.shift_round = a->shift_round;
-    la.y = yq;
-    la.y_dtype = SSDI8_F32;
+    la.y = sum_q;
+    la.y_dtype = ssdi8::kYSums;
     la.workspace = i8;
     la.workspace_bytes = plan.i8.total;
-    const ssdi8_status ls = ssdi8_ssd_chunk_scan(d, &la, stream);
+    const ssdi8_status ls = run_layer(d, &la, stream, true);
     if (ls != SSDI8_OK) return ls;
   }
   if (e == hipSuccess)
-    e = ssdi8::launch_calib_corr(yfp, yq, reinterpret_cast<double*>(ws + plan.part), a->corr,
-                                 d->batch * d->seqlen, H, a->eta, st);
+    e = ssdi8::launch_calib_corr(ld, sum_fp, sum_q, a->corr, a->eta, st);
   return e == hipSuccess ? SSDI8_OK : SSDI8_ERR_HIP;
 }
 

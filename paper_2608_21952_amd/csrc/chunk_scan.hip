@@ -877,7 +877,11 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
   row_block(jta, need_a, ia0, ia1, ya0, ya1);
   row_block(jtb, need_b, ib0, ib1, yb0, yb1);
 
-  if constexpr (sizeof(YT) == 2) {
+  if constexpr (sizeof(YT) == 8) {
+    __syncthreads();
+    fp16::channel_sums(reinterpret_cast<double*>(s_xT), wv, lane, ya0, ya1, yb0, yb1,
+                       y + ((size_t)b * nc + c) * HP + (size_t)h * kP);
+  } else if constexpr (sizeof(YT) == 2) {
     // fp16 output leaves through LDS as whole 128-byte token rows.  The stage reuses the x^T
     // bytes once every wave is done with them: row j at 128 j, its 16-byte column chunk k at
     // slot k ^ (j & 7) (conflict-free 8-byte writes by token and 16-byte reads by row).
@@ -928,7 +932,9 @@ hipError_t launch_chunk_scan(const LayerDims& d, const void* x, int x_dtype, con
       hipLaunchKernelGGL((chunk_scan_kernel<XT, YT, 0>), grid, block, 0, st,                     \
                          SSDI8_SCAN_ARGS(XT, YT));                                               \
   } while (0)
-  if (x_dtype == 1 && y_dtype == 1) SSDI8_SCAN_LAUNCH(_Float16, _Float16);
+  if (x_dtype == 1 && y_dtype == kYSums) SSDI8_SCAN_LAUNCH(_Float16, double);
+  else if (y_dtype == kYSums) SSDI8_SCAN_LAUNCH(float, double);
+  else if (x_dtype == 1 && y_dtype == 1) SSDI8_SCAN_LAUNCH(_Float16, _Float16);
   else if (x_dtype == 1) SSDI8_SCAN_LAUNCH(_Float16, float);
   else if (y_dtype == 1) SSDI8_SCAN_LAUNCH(float, _Float16);
   else SSDI8_SCAN_LAUNCH(float, float);
@@ -959,7 +965,9 @@ hipError_t launch_chunk_scan_fused(const LayerDims& d, const _Float16* x, const 
       hipLaunchKernelGGL((chunk_scan_kernel<_Float16, YT, M>), grid, block, 0, st,               \
                          SSDI8_FUSED_ARGS(YT));                                                  \
   } while (0)
-  if (y_dtype == 1 && fs.speculate) SSDI8_FUSED_LAUNCH(_Float16, 2);
+  if (y_dtype == kYSums && fs.speculate) SSDI8_FUSED_LAUNCH(double, 2);
+  else if (y_dtype == kYSums) SSDI8_FUSED_LAUNCH(double, 1);
+  else if (y_dtype == 1 && fs.speculate) SSDI8_FUSED_LAUNCH(_Float16, 2);
   else if (y_dtype == 1) SSDI8_FUSED_LAUNCH(_Float16, 1);
   else if (fs.speculate) SSDI8_FUSED_LAUNCH(float, 2);
   else SSDI8_FUSED_LAUNCH(float, 1);

@@ -43,9 +43,8 @@ __global__ __launch_bounds__(256) void fp16_bmm_kernel(const T* __restrict__ C,
                                                        float* __restrict__ cb_frag,
                                                        _Float16* __restrict__ bT_frag,
                                                        _Float16* __restrict__ c_frag,
-                                                       float* __restrict__ cb_max,
-                                                       uint32_t* __restrict__ cb_amax, int L,
-                                                       int G, int nc) {
+                                                       float* __restrict__ cb_max, int L, int G,
+                                                       int nc) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[kHalfTok * kBRow];
 
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
@@ -145,7 +144,7 @@ __global__ __launch_bounds__(256) void fp16_bmm_kernel(const T* __restrict__ C,
 #pragma unroll
   for (int u = 0; u < 4; ++u) out[u] = o[u];
   // absolute maximum of the tile's causal entries (the masked ones were staged as 0): ChunkScan2
-  // skips blocks by it (a NaN counts as infinite there)
+  // skips blocks by it (a NaN counts as infinite there), and calibration takes its step from it
   float m = 0.0f;
   bool nan = false;
 #pragma unroll
@@ -159,30 +158,26 @@ __global__ __launch_bounds__(256) void fp16_bmm_kernel(const T* __restrict__ C,
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off, 64));
   const bool any_nan = __ballot(nan) != 0;
-  if (lane == 0) {
+  if (lane == 0)
     cb_max[cg * frag::kCbBlocks + frag::cb_block(jt, it)] = any_nan ? __builtin_inff() : m;
-    // calibration: the same over the group; bit patterns of non-negative floats order like the
-    // floats
-    if (cb_amax) atomicMax(cb_amax + g, __float_as_uint(m));
-  }
 }
 
 }  // namespace
 
 hipError_t launch_fp16_bmm(const LayerDims& d, const void* C, const void* B, int dtype,
                            float* cb_frag, _Float16* bT_frag, _Float16* c_frag, float* cb_max,
-                           uint32_t* cb_amax, hipStream_t st) {
+                           hipStream_t st) {
   const int64_t nwork = (int64_t)d.batch * d.nchunks * d.ngroups * kRoles;
   if (nwork == 0) return hipSuccess;
   if (dtype == 1)
     hipLaunchKernelGGL(fp16_bmm_kernel<_Float16>, dim3((unsigned)nwork), dim3(256), 0, st,
                        static_cast<const _Float16*>(C), static_cast<const _Float16*>(B),
-                       cb_frag, bT_frag, c_frag, cb_max, cb_amax, d.seqlen, d.ngroups,
+                       cb_frag, bT_frag, c_frag, cb_max, d.seqlen, d.ngroups,
                        d.nchunks);
   else
     hipLaunchKernelGGL(fp16_bmm_kernel<float>, dim3((unsigned)nwork), dim3(256), 0, st,
                        static_cast<const float*>(C), static_cast<const float*>(B), cb_frag,
-                       bT_frag, c_frag, cb_max, cb_amax, d.seqlen, d.ngroups, d.nchunks);
+                       bT_frag, c_frag, cb_max, d.seqlen, d.ngroups, d.nchunks);
   return hipGetLastError();
 }
 

@@ -255,5 +255,37 @@ __device__ __forceinline__ void rows_out(const uint8_t* s_y, __amdgpu_buffer_rsr
 }
 static_assert(kP * kXTS >= kQ * kP * 2, "the output stages reuse the x^T bytes");
 
+// Instead of its rows: the fp64 sums over the chunk's 256 tokens of every channel of y, in a fixed
+// order, to out[0 .. 63] (calibration needs only the mean of y; as rows it would be written and
+// read back in fp32).  A lane adds its two rows, then the 32 lanes of a half-wave reduce and
+// scatter in five exchanges, after which lane l % 32 holds register l % 32 of (y0, y1); the four
+// waves add up through LDS (s_sum: 2 KB that nothing else uses any more).
+__device__ __forceinline__ void channel_sums(double* s_sum, int wv, int lane, const v16f& ya0,
+                                             const v16f& ya1, const v16f& yb0, const v16f& yb1,
+                                             double* out) {
+  double v[32];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    v[r] = (double)ya0[r] + (double)yb0[r];
+    v[16 + r] = (double)ya1[r] + (double)yb1[r];
+  }
+#pragma unroll
+  for (int o = 16; o >= 1; o >>= 1) {
+    const bool up = (lane & o) != 0;   // keeps the upper half of the values
+#pragma unroll
+    for (int i = 0; i < o; ++i) {
+      const double keep = up ? v[i + o] : v[i], send = up ? v[i] : v[i + o];
+      v[i] = keep + __shfl_xor(send, o, 64);
+    }
+  }
+  const int r = lane & 31;
+  const int p = 32 * (r >> 4) + 8 * ((r & 15) >> 2) + 4 * (lane >> 5) + (r & 3);
+  s_sum[wv * kP + p] = v[0];
+  __syncthreads();
+  const int t = threadIdx.x;
+  if (t < kP)
+    out[t] = (s_sum[t] + s_sum[kP + t]) + (s_sum[2 * kP + t] + s_sum[3 * kP + t]);
+}
+
 }  // namespace fp16
 }  // namespace ssdi8

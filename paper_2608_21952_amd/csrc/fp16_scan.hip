@@ -127,14 +127,19 @@ __global__ __launch_bounds__(256, 4) void fp16_scan_kernel(
   row_block<XT>(jtb, lane, sm.tab, s_xT, cbrs, cmb, xg, HP, Dh, yb0, yb1, [] {});
 
   // -- output: the two row blocks leave through the x^T bytes as whole token rows
-  const __amdgpu_buffer_rsrc_t yrs = uniform_rsrc(y + tok0 * HP + (size_t)h * kP);
   __syncthreads();
+  if constexpr (sizeof(YT) == 8) {
+    channel_sums(reinterpret_cast<double*>(s_xT), wv, lane, ya0, ya1, yb0, yb1,
+                 y + ((size_t)b * nc + c) * HP + (size_t)h * kP);
+    return;
+  }
+  const __amdgpu_buffer_rsrc_t yrs = uniform_rsrc(y + tok0 * HP + (size_t)h * kP);
   if constexpr (sizeof(YT) == 2) {
     stage_rows_f16(s_xT, jta, lane, ya0, ya1);
     stage_rows_f16(s_xT, jtb, lane, yb0, yb1);
     __syncthreads();
     rows_out<128, 256>(s_xT, yrs, t, HP, 0, stream);
-  } else {
+  } else if constexpr (sizeof(YT) == 4) {
     stage_rows_f32(s_xT, jta, lane, ya0, ya1);
     __syncthreads();
     rows_out<256, 256>(s_xT, yrs, t, HP, 0, stream);
@@ -153,12 +158,14 @@ hipError_t launch_fp16_scan(const LayerDims& d, const void* x, int x_dtype, cons
                             const float* D, void* y, int y_dtype, hipStream_t st) {
   const int64_t nwork = (int64_t)d.batch * d.nchunks * d.nheads;
   if (nwork == 0) return hipSuccess;
-  const int stream = stream_xy(d, x_dtype == 1 ? 2 : 4, y_dtype == 1 ? 2 : 4);
+  const int stream = stream_xy(d, x_dtype == 1 ? 2 : 4, y_dtype == kYSums ? 0 : y_dtype == 1 ? 2 : 4);
 #define SSDI8_F16SCAN_LAUNCH(XT, YT)                                                           \
   hipLaunchKernelGGL((fp16_scan_kernel<XT, YT>), dim3((unsigned)nwork), dim3(256), 0, st,       \
                      static_cast<const XT*>(x), dt, A, c_frag, pin, cb, cb_max, D, dt_softplus, \
                      static_cast<YT*>(y), d.seqlen, d.nheads, d.ngroups, d.nchunks, stream)
-  if (x_dtype == 1 && y_dtype == 1) SSDI8_F16SCAN_LAUNCH(_Float16, _Float16);
+  if (x_dtype == 1 && y_dtype == kYSums) SSDI8_F16SCAN_LAUNCH(_Float16, double);
+  else if (y_dtype == kYSums) SSDI8_F16SCAN_LAUNCH(float, double);
+  else if (x_dtype == 1 && y_dtype == 1) SSDI8_F16SCAN_LAUNCH(_Float16, _Float16);
   else if (x_dtype == 1) SSDI8_F16SCAN_LAUNCH(_Float16, float);
   else if (y_dtype == 1) SSDI8_F16SCAN_LAUNCH(float, _Float16);
   else SSDI8_F16SCAN_LAUNCH(float, float);

@@ -11,6 +11,10 @@ namespace ssdi8 {
 // start and end (hipExtLaunchKernelGGL: the dispatch's timestamps, the figures a profiler's
 // kernel trace reports) rather than markers recorded between kernels.
 
+// y_dtype of the scan launchers beside 0 (fp32) and 1 (fp16): y is [batch, nchunks, nheads, 64]
+// fp64, the sum of every channel over the tokens of a chunk, instead of the rows.
+constexpr int kYSums = 2;
+
 // Sizes shared by the SSD-layer kernels (P = 64, N = 128, Q = 256 fixed).
 struct LayerDims {
   int batch, seqlen, nheads, ngroups, nchunks;
@@ -138,7 +142,7 @@ hipError_t launch_decode(int64_t batch, int64_t nheads, int64_t ngroups, const v
 // ChunkScan1's operand), ChunkScan.
 hipError_t launch_fp16_bmm(const LayerDims& d, const void* C, const void* B, int dtype,
                            float* cb_frag, _Float16* bT_frag, _Float16* c_frag, float* cb_max,
-                           uint32_t* cb_amax, hipStream_t st);
+                           hipStream_t st);
 hipError_t launch_fp16_state(const LayerDims& d, const void* x, int x_dtype, const float* dt,
                              int dt_softplus, const float* A, const _Float16* bT_frag, float* S,
                              float* dec, hipStream_t st);
@@ -156,21 +160,19 @@ hipError_t launch_fp16_walk(const LayerDims& d, const void* x, int x_dtype, cons
                             const float* init, _Float16* pin, float* final_state,
                             hipStream_t st);
 
-// Calibration (static steps and the mean correction): absmax words cleared by a fill kernel,
-// absmax of X_scaled, fp states from split fp16 operands with their absmax, the steps, the
-// correction from two fp32 layer outputs.
+// Calibration (static steps and the mean correction): absmax words cleared by a fill kernel, absmax
+// of X_scaled and fp states from split fp16 operands with their absmax, the steps (C.B^T's from
+// ChunkBMM's block maxima), the correction from the channel sums of two layers.
 hipError_t launch_calib_zero(uint32_t* p, int n, hipStream_t st);
-hipError_t launch_calib_xs(const LayerDims& d, const void* x, int x_dtype, const float* dt,
-                           int dt_softplus, const float* A, uint32_t* xs_amax, hipStream_t st);
 hipError_t launch_calib_states(const LayerDims& d, const void* x, int x_dtype, const float* dt,
                                int dt_softplus, const float* A, const _Float16* bT_frag,
-                               float* S, double* dec64, uint32_t* s_amax, hipStream_t st);
-hipError_t launch_calib_steps(const uint32_t* xs_amax, const uint32_t* s_amax,
-                              const uint32_t* cb_amax, float* aXs, float* aS, float* aCB, int H,
-                              int G, int xs_per_head, hipStream_t st);
-size_t calib_corr_scratch_bytes(int H);
-hipError_t launch_calib_corr(const float* y_fp, const float* y_q, double* part, float* corr,
-                             int64_t T, int H, float eta, hipStream_t st);
+                               uint32_t* xs_amax, float* S, double* dec64, uint32_t* s_amax,
+                               hipStream_t st);
+hipError_t launch_calib_steps(const LayerDims& d, const uint32_t* xs_amax, const uint32_t* s_amax,
+                              const float* cb_max, float* aXs, float* aS, float* aCB,
+                              int xs_per_head, hipStream_t st);
+hipError_t launch_calib_corr(const LayerDims& d, const double* s_fp, const double* s_q,
+                             float* corr, float eta, hipStream_t st);
 
 // MFMA peak probe (int8 32x32x32 for dtype 0, fp16 32x32x16 otherwise): `blocks` workgroups of
 // 4 waves, each running 4 independent chains of `iters` MFMAs; one value per thread to `out`.

@@ -151,3 +151,34 @@ def test_correction_is_the_damped_mean_of_the_layer_difference(torch, ssdi8):
     before = d.mean(axis=(0, 1))
     np.testing.assert_allclose(rest, (1 - ETA) * before,
                                atol=1e-6 * float(np.abs(before).max()) + 1e-7)
+
+
+@pytest.mark.parametrize("B,L,H,G,dtype", [
+    (1, 256, 3, 3, "fp16"),     # one chunk: one row per layer, the single pass
+    (1, 1280, 5, 1, "fp16"),    # five chunks of few sequences: the separate kernels
+    (3, 768, 6, 2, "fp32"),     # fp32 x, nine rows
+    (2, 1280, 60, 4, "fp16"),   # the speculative single pass, the walked FP16 states
+])
+def test_correction_from_channel_sums(torch, ssdi8, B, L, H, G, dtype):
+    """corr is eta times the mean of the two layers' own fp32 outputs: the kernels sum the same
+    fp32 values in fp64, so only the order of those sums (2^-53 of the sum of |y| each) and the
+    last rounding to fp32 differ.  alpha_CB is the largest causal entry of fp16 C B^T / 127, summed
+    in fp32 here and there: 128 terms, 1e-5 of it."""
+    torch.manual_seed(B + L + H)
+    dt_ = torch.float16 if dtype == "fp16" else torch.float32
+    x = (torch.randn(B, L, H, 64, device="cuda") * 3).to(dt_)
+    dt = torch.randn(B, L, H, device="cuda") * 0.5 - 2
+    A, D = -torch.exp(torch.rand(H, device="cuda") * 6 - 4), torch.rand(H, device="cuda")
+    Bt, Ct = (torch.randn(B, L, G, 128, device="cuda").to(dt_) for _ in range(2))
+    s = ssdi8.calibrate(x, dt, A, Bt, Ct, D=D, eta=0.5)
+    yf = ssdi8.ssd_chunk_scan_fp16(x, dt, A, Bt, Ct, D=D, y_dtype=torch.float32)["y"].double()
+    yq = ssdi8.ssd_chunk_scan(x, dt, A, None, None, s["alpha_B"], s["alpha_C"], s["alpha_Xs"],
+                              s["alpha_S"], s["alpha_CB"], D=D, B=Bt, C=Ct,
+                              y_dtype=torch.float32)["y"].double()
+    ref = 0.5 * (yf - yq).mean((0, 1))
+    slack = 2.0 ** -24 * ref.abs() + 2.0 ** -48 * (yf.abs() + yq.abs()).mean((0, 1))
+    assert bool(((s["corr"].double() - ref).abs() <= slack).all())
+    c, b = (t.half().float().view(B, L // 256, 256, G, 128).permute(0, 1, 3, 2, 4).contiguous()
+            for t in (Ct, Bt))
+    cb = (c @ b.transpose(3, 4).contiguous()).tril().abs().amax((0, 1, 3, 4)) / 127.0
+    assert bool(((s["alpha_CB"] - cb).abs() <= 1e-5 * cb).all())
