@@ -1,12 +1,16 @@
 // FP16 baseline, ChunkBMM (Alg. 2 module 4 without quantization):
 //   CB[j, i] = sum_n C[j, n] B[i, n]   for i <= j   (fp16 MFMA 32x32x16, fp32 accumulation)
-// stored in fp32, as the 36 causal 32x32 blocks of each (b, c, g) in the fragment order in which
-// ChunkScan2 builds its weights (frag::cb_inblock, in fp32 elements).  Like the INT8 ChunkBMM it
-// also leaves the operands of the later kernels in fragment order: C rows of the chunk
+// stored in fp32, as the 36 causal 32x32 blocks of each (b, c, g) in the lane order in which
+// ChunkScan2 builds its weights (frag::cb_inblock's 16 elements of a lane), in four planes: plane u
+// holds elements 4 u .. 4 u + 3 of all lanes, so that every 16-byte load and store of a wave covers
+// 1 KB.  With a lane's 64 bytes together each instruction touched 64 lines (64 chunk-groups: this
+// kernel 11.5 -> 10.3 us; ChunkScan of 80 heads 104 -> 99.5 us).  Like the INT8 ChunkBMM it also
+// leaves the operands of the later kernels in fragment order: C rows of the chunk
 // (ChunkScan1, K = n; frag::pk16_offset) and B^T of the chunk (ChunkState, rows n, K = tokens;
 // frag::k16_offset).
-// Work item = (b, c, g, role): roles 0..8 compute 4 causal tiles each (one per wave), role 9
-// transposes B.
+// Work item = (b, c, g, role): roles 0..8 compute 4 causal tiles each (one per wave), roles 9 and
+// 10 transpose half of B each (one for all of it outlived the tiles, 10.7 -> 10.45 us; four of 64
+// tokens: 13.0 us against 11.6 us for one, before the plane order).
 #include "common.hpp"
 #include "frag.hpp"
 #include "launch.hpp"
@@ -16,8 +20,8 @@ namespace ssdi8 {
 namespace {
 
 constexpr int kTileWGs = 9;
-constexpr int kRoles = kTileWGs + 1;
-constexpr int kHalfTok = kQ / 2;       // tokens per transposer pass
+constexpr int kRoles = kTileWGs + 2;
+constexpr int kHalfTok = kQ / 2;       // tokens per transposer
 constexpr int kBRow = kN * 2 + 16;     // LDS bytes per staged B row (fp16)
 constexpr int kStS = 36;               // floats per row of a wave's 32x32 fp32 stage
 
@@ -61,31 +65,28 @@ __global__ __launch_bounds__(256) void fp16_bmm_kernel(const T* __restrict__ C,
   const T* bbase = B + tok0 * rs + (size_t)g * kN;
   const size_t cg = ((size_t)b * nc + c) * G + g;
 
-  if (role == kTileWGs) {
-    // ---- B^T of the chunk in two passes of 128 tokens: stage the rows as fp16, then each
-    //      thread assembles 16-byte runs of 8 tokens of one channel n
+  if (role >= kTileWGs) {
+    // ---- B^T of 128 tokens of the chunk: stage the rows as fp16, then each thread
+    //      assembles 16-byte runs of 8 tokens of one channel n
     _Float16* dst = bT_frag + cg * (size_t)kN * kQ;
-    for (int pass = 0; pass < 2; ++pass) {
-      const int j0p = pass * kHalfTok;
+    const int j0p = (role - kTileWGs) * kHalfTok;
 #pragma unroll
-      for (int k = 0; k < (kHalfTok * kN) / (8 * 256); ++k) {
-        const int idx = k * 256 + t;
-        const int j = idx >> 4, col = (idx & 15) * 8;
-        *reinterpret_cast<h8*>(smem + j * kBRow + col * 2) =
-            load8<T>(bbase + (size_t)(j0p + j) * rs + col);
-      }
-      __syncthreads();
+    for (int k = 0; k < (kHalfTok * kN) / (8 * 256); ++k) {
+      const int idx = k * 256 + t;
+      const int j = idx >> 4, col = (idx & 15) * 8;
+      *reinterpret_cast<h8*>(smem + j * kBRow + col * 2) =
+          load8<T>(bbase + (size_t)(j0p + j) * rs + col);
+    }
+    __syncthreads();
 #pragma unroll
-      for (int k = 0; k < (kHalfTok / 8) * kN / 256; ++k) {
-        const int unit = k * 256 + t;
-        const int n = unit & (kN - 1), jg = unit >> 7;   // channel, group of 8 tokens
-        h8 v;
+    for (int k = 0; k < (kHalfTok / 8) * kN / 256; ++k) {
+      const int unit = k * 256 + t;
+      const int n = unit & (kN - 1), jg = unit >> 7;   // channel, group of 8 tokens
+      h8 v;
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          v[e] = *reinterpret_cast<const _Float16*>(smem + (jg * 8 + e) * kBRow + n * 2);
-        *reinterpret_cast<h8*>(dst + frag::k16_offset(n, j0p + jg * 8, kQ)) = v;
-      }
-      __syncthreads();
+      for (int e = 0; e < 8; ++e)
+        v[e] = *reinterpret_cast<const _Float16*>(smem + (jg * 8 + e) * kBRow + n * 2);
+      *reinterpret_cast<h8*>(dst + frag::k16_offset(n, j0p + jg * 8, kQ)) = v;
     }
     return;
   }
@@ -140,9 +141,9 @@ __global__ __launch_bounds__(256) void fp16_bmm_kernel(const T* __restrict__ C,
     o[2 * ks + 1] = *reinterpret_cast<const float4*>(st + jj * kStS + 16 * ks + 8 * half + 4);
   }
   float4* out = reinterpret_cast<float4*>(cb_frag + (cg * frag::kCbBlocks + frag::cb_block(jt, it)) *
-                                          1024 + lane * 16);
+                                          1024 + lane * 4);
 #pragma unroll
-  for (int u = 0; u < 4; ++u) out[u] = o[u];
+  for (int u = 0; u < 4; ++u) out[64 * u] = o[u];
   // absolute maximum of the tile's causal entries (the masked ones were staged as 0): ChunkScan2
   // skips blocks by it (a NaN counts as infinite there), and calibration takes its step from it
   float m = 0.0f;

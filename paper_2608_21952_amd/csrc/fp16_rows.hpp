@@ -100,7 +100,7 @@ __device__ __forceinline__ void row_block(int jt, int lane, const Tables& T, con
                                           size_t HP, float Dh, v16f& y0, v16f& y1, F&& late) {
   asm volatile("" : "+s"(jt) :: "memory");
   const int pc = lane & 31, half = lane >> 5;
-  const uint32_t lane64 = lane * 64;
+  const uint32_t lane16 = lane * 16;
   const int jrow = jt * 32 + pc;
   const float csrj = T.csr[jrow];
   const float ej = __expf(csrj);
@@ -155,9 +155,9 @@ __device__ __forceinline__ void row_block(int jt, int lane, const Tables& T, con
     y0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa0, wf, y0, 0, 0, 0);
     y1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa1, wf, y1, 0, 0, 0);
   };
-  auto load_block = [&](uint32_t off, uint4 (&v)[4]) {
+  auto load_block = [&](uint32_t off, uint4 (&v)[4]) {   // four planes of 1 KB (fp16_bmm.hip)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = buf_load16(cbrs, lane64, off + 16 * u);
+    for (int u = 0; u < 4; ++u) v[u] = buf_load16(cbrs, lane16, off + 1024 * u);
   };
   auto cbv = [](const uint4 (&v)[4], int k) {   // float k of this lane's 16
     const uint4 q = v[k >> 2];

@@ -11,8 +11,8 @@
 // x / y stream.  So each wave runs Scan1 of both of its row blocks from one load of P_in (64 KB
 // per workgroup; per row block, in fp32, it was 256 KB), its result seeds the Scan2 accumulators,
 // and CB blocks that decay makes zero weights of are not loaded.  124 VGPRs and 37 KB of LDS keep
-// four workgroups per CU (three before).  2.7B-shaped layer, slow heads included: 209 -> 128 us;
-// 130M-shaped: 51.5 -> 36.5 us.
+// four workgroups per CU (three before).  2.7B-shaped layer, slow heads included: 209 -> 99.5 us;
+// 130M-shaped: 51.5 -> 33.8 us.
 #include "common.hpp"
 #include "fp16_rows.hpp"
 #include "frag.hpp"

@@ -81,15 +81,6 @@ __host__ __device__ __forceinline__ size_t k16_offset(int row, int k, int K) {
   return ((size_t)(row >> 5) * (K >> 4) + (k >> 4)) * 512 + lane * 8 + (k & 7);
 }
 
-// Inverse of k16_offset.
-__host__ __device__ __forceinline__ void k16_coords(size_t off, int K, int* row, int* k) {
-  const size_t tile = off >> 9;
-  const int kt = K >> 4;
-  const int lane = (int)((off >> 3) & 63);
-  *row = (int)(tile / kt) * 32 + (lane & 31);
-  *k = (int)(tile % kt) * 16 + 8 * (lane >> 5) + (int)(off & 7);
-}
-
 // Permuted k16 order (pk16): the same tiles, with the 16 K values dealt to the two half-waves in
 // runs of 4: lane l holds, in slot e, k = 8 (e / 4) + 4 (l / 32) + e % 4.  As with pk above, a
 // 32x32 MFMA result whose rows are K leaves its lanes in exactly this order (registers 8 kb .. 8
