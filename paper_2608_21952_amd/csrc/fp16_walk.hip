@@ -10,11 +10,13 @@
 // token per thread for its ChunkCumsum) while waves 4 .. 7, each one 32-wide n-tile of the state
 // for all channels, multiply chunk c with B^T fragments requested a chunk ahead.
 //
-// 2.7B-shaped layer, 320 sequences of 16 chunks: 102 us for the 80 + 41 us of ChunkState and
+// 2.7B-shaped layer, 320 sequences of 16 chunks: 100 us for the 80 + 41 us of ChunkState and
 // StatePassing (252 instead of 588 MB), and ChunkScan after it 109 instead of 130 us (x is still
-// in the Infinity Cache).  What bounds it: x in flight (without its x loads it takes 56 us, the
-// chain of barriers per chunk); 32 four-byte loads per thread and chunk stalled on the 63 a wave
-// can have counted, so x comes in 16-byte runs.
+// in the Infinity Cache).  What bounds it: the chain of a chunk (softplus, scan, LUT, X~, with two
+// barriers; a third one for X~ cost 6 to 20 %: 128, 192, 256 and 320 sequences of 16 chunks 53.6,
+// 55.6, 62.0 and 107 us, now 42.6, 48.0, 55.6 and 99.8), beside a second workgroup on the same CU:
+// 257 sequences take what 512 do (101 us).  32 four-byte loads per thread and chunk stalled on
+// the 63 a wave can have counted, so x comes in 16-byte runs.
 #include "common.hpp"
 #include "fp16_rows.hpp"
 #include "frag.hpp"
@@ -62,8 +64,10 @@ __global__ __launch_bounds__(kThreads, 4) void fp16_walk_kernel(
   const int g = __builtin_amdgcn_readfirstlane(h / (H / G));
   uint32_t* sr = reinterpret_cast<uint32_t*>(sm.scan + 4);
 
-  // Both roles pass the same barriers: three per chunk (scan totals, LUT, X~), a fourth when the
-  // scan is inexact (the test reads the same words in every wave).
+  // Both roles pass the same barriers: two per chunk (scan totals, LUT), a third when the scan is
+  // inexact (the test reads the same words in every wave).  X~ and the decay of chunk c are there
+  // for the consumers after the scan barrier of chunk c + 1, and its buffers are written again
+  // after the one of chunk c + 2, which the consumers reach when they have read them.
   if (wv < 4) {
     // ---- x -> X~, one chunk ahead of the products
     // this thread: channels [8 ch, 8 ch + 8) of tokens [8 tg, 8 tg + 8), one 16-byte (fp32: two)
@@ -147,7 +151,6 @@ __global__ __launch_bounds__(kThreads, 4) void fp16_walk_kernel(
             make_uint4(w[0], w[1], w[2], w[3]);
       }
       load(cc + kAhead, xv, dv);
-      __syncthreads();
     };
     load(0, xr[0], dtr[0]);
     if constexpr (kAhead == 2) load(1, xr[1], dtr[1]);
@@ -192,7 +195,7 @@ __global__ __launch_bounds__(kThreads, 4) void fp16_walk_kernel(
     };
     pass_scan();          // chunk 0
     __syncthreads();
-    __syncthreads();
+    if (nc > 0) pass_scan();   // chunk 1: X~ of chunk 0 is there
     for (int c = 0; c < nc; ++c) {
       _Float16* dst = pin + (((size_t)b * nc + c) * H + h) * (size_t)kP * kN +
                       (size_t)(2 * nt) * 512 + lane * 8;
@@ -211,6 +214,7 @@ __global__ __launch_bounds__(kThreads, 4) void fp16_walk_kernel(
         P0[r] *= d;
         P1[r] *= d;
       }
+      __syncthreads();   // LUT of chunk c + 1
       const __amdgpu_buffer_rsrc_t brs = b_rsrc(c + 1);
       const uint8_t* xs = sm.xs[c & 1];
       // opaque per chunk: its addresses are formed here and not held across the loop
@@ -226,9 +230,7 @@ __global__ __launch_bounds__(kThreads, 4) void fp16_walk_kernel(
         P1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf, a1, P1, 0, 0, 0);
         f[ks] = buf_load16(brs, lane16, 1024 * ks);
       }
-      pass_scan();        // chunk c + 1
-      __syncthreads();
-      __syncthreads();
+      if (c + 1 < nc) pass_scan();   // chunk c + 2: X~ of chunk c + 1 is there
     }
     if (final_state) {
       int l = threadIdx.x & 63;
