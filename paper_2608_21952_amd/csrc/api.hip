@@ -119,11 +119,12 @@ Fp16Plan plan_fp16(const ssdi8_dims* d) {
 }
 
 // Whether the FP16 layer's ChunkState and StatePassing run as the kernel that walks the sequences:
-// its chunks are serial, so it takes enough of them in flight.  Whole layer, separate / walk, slow
-// heads included: 48 sequences x 32 chunks 81 / 118 us, 80 x 64 267 / 311, 96 x 16 80 / 85,
-// 96 x 32 169 / 149, 112 x 32 196 / 170, 128 x 128 814 / 775, 192 x 8 84 / 76, 320 x 16 257 / 216,
-// 640 x 8 260 / 193, 1024 x 1 61 / 55.
-bool fp16_walks(const LayerDims& ld) { return (int64_t)ld.batch * ld.nheads >= 112; }
+// its chunks are serial, so it takes enough of them in flight.  Whole layer in a graph, separate /
+// walk, slow heads included: 48 sequences x 16 chunks 50 / 63 us, 64 x 32 95 / 114, 80 x 4 38 / 36,
+// 80 x 16 68 / 74, 80 x 64 257 / 297, 96 x 2 31 / 28, 96 x 16 78.5 / 78.2, 96 x 32 178 / 151,
+// 112 x 32 196 / 154, 128 x 128 806 / 733, 320 x 1 38 / 31, 384 x 4 79 / 66; fp32 x: 80 x 16 93 /
+// 98, 96 x 16 108 / 105, 96 x 32 277 / 269.
+bool fp16_walks(const LayerDims& ld) { return (int64_t)ld.batch * ld.nheads >= 96; }
 
 struct CalibPlan {
   Fp16Plan f16;
