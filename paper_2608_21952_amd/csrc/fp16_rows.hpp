@@ -58,7 +58,7 @@ struct Tables {
   float dg[kQ];        // dt_i exp(r_{I-1} - cs_i) if block I has a small span, else dt_i
   float csr[kQ];       // cs_i - r_{I-1}
   float R[8][8];       // exp(r_a - r_b), b <= a
-  float umax[8];       // max |u_i| over block I (inf if one is NaN)
+  float umax[8];       // max |u_i| over block I (inf if one is NaN or an x is not finite)
   double r[8];
 };
 

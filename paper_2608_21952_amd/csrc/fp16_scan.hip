@@ -76,6 +76,7 @@ __global__ __launch_bounds__(256, 4) void fp16_scan_kernel(
   {
     uint8_t* r0 = s_xT + p0 * kXTS + jb * 64;
     uint8_t* r1 = r0 + kXTS;
+    h2_t fin = {};   // 0, NaN where one of the values is not finite
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       uint32_t a[4], bb[4];
@@ -84,10 +85,15 @@ __global__ __launch_bounds__(256, 4) void fp16_scan_kernel(
         const int r = 8 * q + 2 * u;
         a[u] = (uint32_t)Pair<XT>::lo(xr[r]) | ((uint32_t)Pair<XT>::lo(xr[r + 1]) << 16);
         bb[u] = (uint32_t)Pair<XT>::hi(xr[r]) | ((uint32_t)Pair<XT>::hi(xr[r + 1]) << 16);
+        fin = __builtin_elementwise_fma(__builtin_bit_cast(h2_t, a[u]), (h2_t){}, fin);
+        fin = __builtin_elementwise_fma(__builtin_bit_cast(h2_t, bb[u]), (h2_t){}, fin);
       }
       *reinterpret_cast<uint4*>(r0 + 16 * q) = make_uint4(a[0], a[1], a[2], a[3]);
       *reinterpret_cast<uint4*>(r1 + 16 * q) = make_uint4(bb[0], bb[1], bb[2], bb[3]);
     }
+    // A zero weight times an infinite or NaN x is NaN, so the blocks of these 32 tokens are not
+    // skipped then (this wave wrote umax[jb] in build_tables; one instruction per pair of x)
+    if (!(fin.x == fin.x && fin.y == fin.y)) sm.tab.umax[jb] = __builtin_inff();
   }
   __syncthreads();
 

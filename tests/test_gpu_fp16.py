@@ -151,3 +151,24 @@ def test_fp16_walk_matches_oracle(torch, ssdi8, batch, seqlen, nheads, ngroups, 
     for (b, h) in picks:
         assert_close(y[b, :, h], ref["slabs"][(b, h)]["y64"], f"y slab ({b},{h})")
         _check_state(fin[b, h], ref["slabs"][(b, h)]["final"], f"final state slab ({b},{h})")
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "fp32"])
+@pytest.mark.parametrize("value,token", [(float("inf"), 3), (float("nan"), 70),
+                                         (float("-inf"), 255)])
+def test_fp16_scan_non_finite_x(torch, ssdi8, dtype, value, token):
+    """An infinite or NaN x reaches every later row of its channel, also through blocks whose
+    weights decay to zero (zero times infinity is NaN), and no other channel."""
+    torch.manual_seed(3)
+    dt_ = torch.float16 if dtype == "fp16" else torch.float32
+    B, L, H = 1, 512, 2
+    x = torch.randn(B, L, H, 64, device="cuda").to(dt_)
+    dt = torch.zeros(B, L, H, device="cuda")
+    A = torch.tensor([-200.0, -0.1], device="cuda")
+    Bt, Ct = (torch.randn(B, L, 1, 128, device="cuda").to(dt_) for _ in range(2))
+    x[0, token, :, 5] = value
+    y = ssdi8.ssd_chunk_scan_fp16(x, dt, A, Bt, Ct, D=torch.ones(H, device="cuda"))["y"]
+    fin = torch.isfinite(y)
+    assert not bool(fin[0, token:, :, 5].any())
+    fin[..., 5] = True
+    assert bool(fin.all())
