@@ -189,12 +189,17 @@ bool single_pass(const ssdi8_dims* d, const ssdi8_scan_args* a) {
   if (a->path != 0) return a->path == 2;
   // automatic: the single pass hides its chains of hand-offs behind enough concurrent sequences.
   // Taken where the chains are longest (slowly decaying heads, no chunk with a zero Q(Decay)).
-  // Layer us, separate / single: one chunk 28 / 23 (8 to 64 sequences; no hand-off), four chunks
-  // 28 / 26 (8), 28 / 27 (24), 32 / 29 (64); 8 chunks 30 / 32 (24); 16 chunks 48 / 50 (48), 53 / 53
-  // (56), 55 / 52 (64), 65 / 60 (80); 32 chunks 48 / 62 (24), 71 / 67 (48)
+  // Layer us, separate / single, 8, 24 and 48 sequences: one chunk 27.0 / 22.3, 27.1 / 22.4, 27.7 /
+  // 22.5 (no hand-off), two 26.8 / 24.7, 27.1 / 24.7, 28.0 / 25.0, three 27.2 / 25.0, 27.5 / 25.3, 28.6
+  // / 25.9, four 26.7 / 25.9, 27.6 / 26.1, 28.6 / 27.2, five 27.6 / 26.5, 28.3 / 26.8, 30.2 / 28.1, six
+  // 27.4 / 28.5, 28.3 / 29.1, 32.7 / 33.1, eight 26.7 / 29.8, 28.3 / 31.4, 36.0 / 35.7; 16 chunks 48 /
+  // 50 (48), 53 / 53 (56), 55 / 52 (64), 65 / 60 (80); 32 chunks 48 / 62 (24), 71 / 67 (48).
+  // From 64 sequences on, two and three chunks keep the separate kernels: that selection is part
+  // of the tested interface (test_abi_cpu.py)
   const int64_t nc = d->chunk > 0 ? d->seqlen / d->chunk : 0;
   const int64_t bh = d->batch * d->nheads;
-  return nc == 1 || nc == 4 || (bh >= 64 && nc >= 4) || (bh >= 48 && nc >= 32);
+  if (nc == 2 || nc == 3) return bh < 64;
+  return nc == 1 || nc == 4 || nc == 5 || (bh >= 64 && nc >= 4) || (bh >= 48 && nc >= 32);
 }
 
 // ssdi8_ssd_chunk_scan; with `sums` y is the channel sums of calibration (y_dtype kYSums).

@@ -444,14 +444,16 @@ def test_traffic_source_hash_ignores_comments_only():
 
 
 def test_single_pass_selection_few_chunks(ssdi8):
-    """One chunk has no hand-off and four chunks a short chain: the single pass at any number of
-    sequences; more chunks from 64 sequences on."""
+    """Up to five chunks are a short chain: the single pass for few sequences; more chunks from 64
+    sequences on."""
     import torch
     use = lambda *d: ssdi8.uses_single_pass(ssdi8.dims(*d), torch.float16)
     assert use(1, 256, 1, 1) and use(1, 256, 512, 1)
-    assert use(1, 1024, 8, 1) and use(1, 1024, 64, 1)
-    assert not use(1, 1280, 24, 1) and not use(1, 1280, 63, 1)
-    assert use(1, 1280, 64, 1) and use(2, 4096, 32, 1)
+    assert use(1, 512, 8, 1) and use(1, 768, 63, 1) and not use(1, 768, 64, 1)
+    assert use(1, 1024, 8, 1) and use(1, 1280, 8, 1) and use(1, 1280, 64, 1)
+    assert not use(1, 0, 64, 1)
+    assert not use(1, 1536, 24, 1) and not use(1, 1536, 63, 1)
+    assert use(1, 1536, 64, 1) and use(2, 4096, 32, 1)
 
 
 def test_native_marshalling_leaves_the_errors_to_python(ssdi8):

@@ -535,7 +535,7 @@ def test_native_marshalling_forms(torch, ssdi8):
     assert torch.equal(c["y"], a["y"])
 
 
-@pytest.mark.parametrize("H,nc", [(1, 1), (24, 1), (3, 4), (64, 5)])
+@pytest.mark.parametrize("H,nc", [(1, 1), (24, 1), (5, 2), (63, 3), (3, 4), (7, 5), (64, 6)])
 def test_single_pass_few_chunks(torch, ssdi8, H, nc):
     """The sizes the automatic choice gives to the single pass with few chunks: identical to the
     separate kernels, no wait runs out."""
