@@ -123,7 +123,10 @@ Fp16Plan plan_fp16(const ssdi8_dims* d) {
 // walk, slow heads included: 48 sequences x 16 chunks 50 / 63 us, 64 x 32 95 / 114, 80 x 4 38 / 36,
 // 80 x 16 68 / 74, 80 x 64 257 / 297, 96 x 2 31 / 28, 96 x 16 78.5 / 78.2, 96 x 32 178 / 151,
 // 112 x 32 196 / 154, 128 x 128 806 / 733, 320 x 1 38 / 31, 384 x 4 79 / 66; fp32 x: 80 x 16 93 /
-// 98, 96 x 16 108 / 105, 96 x 32 277 / 269.
+// 98, 96 x 16 108 / 105, 96 x 32 253 / 235.  Above 256 sequences (a second workgroup on some CUs):
+// 257 x 16 219 / 171, 272 x 64 867 / 822, 288 x 16 222 / 183, 300 x 16 229 / 184; fp32 x: 257 x 16
+// 369 / 310, 300 x 16 388 / 354.  Against it: the longest walks of the fewest sequences, 96 x 128 628
+// / 663 (fp32 x: 976 / 1022).
 bool fp16_walks(const LayerDims& ld) { return (int64_t)ld.batch * ld.nheads >= 96; }
 
 struct CalibPlan {

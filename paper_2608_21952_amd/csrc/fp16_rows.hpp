@@ -17,6 +17,28 @@ typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_h2(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2_t){a, b}, h2_t));
 }
+// Two tokens' X~ = LUT x of one channel as packed fp16: the exact product rounded once, to fp16
+// (left to the compiler it is rounded once or, through fp32, twice, depending on how the result is
+// packed: 4.7e-6 of the final state).  fp16 x: channel `half` of the tokens' pairs w0, w1.
+template <int half>
+__device__ __forceinline__ uint32_t lut_x2(float l0, uint32_t w0, float l1, uint32_t w1) {
+  uint32_t d;
+  if constexpr (half == 0)
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0 op_sel_hi:[0,1,0]\n\t"
+        "v_fma_mixhi_f16 %0, %3, %4, 0 op_sel_hi:[0,1,0]"
+        : "=&v"(d) : "v"(l0), "v"(w0), "v"(l1), "v"(w1));
+  else
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0 op_sel:[0,1,0] op_sel_hi:[0,1,0]\n\t"
+        "v_fma_mixhi_f16 %0, %3, %4, 0 op_sel:[0,1,0] op_sel_hi:[0,1,0]"
+        : "=&v"(d) : "v"(l0), "v"(w0), "v"(l1), "v"(w1));
+  return d;
+}
+__device__ __forceinline__ uint32_t lut_x2(float l0, float x0, float l1, float x1) {
+  uint32_t d;
+  asm("v_fma_mixlo_f16 %0, %1, %2, 0\n\tv_fma_mixhi_f16 %0, %3, %4, 0"
+      : "=&v"(d) : "v"(l0), "v"(x0), "v"(l1), "v"(x1));
+  return d;
+}
 
 // Two adjacent channels of one token row, loaded raw.
 template <typename XT> struct Pair;
@@ -34,6 +56,13 @@ template <> struct Pair<_Float16> {
   static __device__ __forceinline__ float hif(raw v) {
     return (float)__builtin_bit_cast(_Float16, hi(v));
   }
+  // X~ of tokens 0 and 1: channel lo, channel hi
+  static __device__ __forceinline__ uint32_t lut_lo(float l0, raw v0, float l1, raw v1) {
+    return lut_x2<0>(l0, v0, l1, v1);
+  }
+  static __device__ __forceinline__ uint32_t lut_hi(float l0, raw v0, float l1, raw v1) {
+    return lut_x2<1>(l0, v0, l1, v1);
+  }
 };
 template <> struct Pair<float> {
   typedef float2 raw;
@@ -50,6 +79,12 @@ template <> struct Pair<float> {
   }
   static __device__ __forceinline__ float lof(raw v) { return v.x; }
   static __device__ __forceinline__ float hif(raw v) { return v.y; }
+  static __device__ __forceinline__ uint32_t lut_lo(float l0, raw v0, float l1, raw v1) {
+    return lut_x2(l0, v0.x, l1, v1.x);
+  }
+  static __device__ __forceinline__ uint32_t lut_hi(float l0, raw v0, float l1, raw v1) {
+    return lut_x2(l0, v0.y, l1, v1.y);
+  }
 };
 
 // ChunkScan's decay tables of a chunk (r_t = cs at the last token of 32-token block t, r_{-1} = 0).

@@ -1,7 +1,7 @@
 // FP16 baseline, ChunkCumsum + ChunkState and StatePassing (Alg. 2 modules 1-3 without
 // quantization):
 //   dt, dA, cs, LUT_state    as in the INT8 ChunkState (fp64 softplus and in-chunk sum)
-//   X~       = fp16(fl32(LUT_j x_jp))
+//   X~       = fp16(LUT_j x_jp), the exact product rounded once
 //   S[p, n]  = sum_j X~[j, p] B[j, n]       fp16 MFMA 32x32x16 over tokens, fp32 accumulation
 //   d        = fl32(exp(cs_last))
 //   P_in[c+1] = fl32(d P_in[c] + S[c])      one fma per element, fp32 states
@@ -21,28 +21,6 @@ namespace {
 constexpr int kXS = kQ * 2 + 16;   // LDS bytes per channel row of X~^T (fp16)
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-
-template <typename XT> struct Pair;
-template <> struct Pair<_Float16> {
-  typedef uint32_t raw;
-  static __device__ __forceinline__ raw load(const _Float16* p) {
-    return *reinterpret_cast<const uint32_t*>(p);
-  }
-  static __device__ __forceinline__ float lo(raw v) {
-    return (float)__builtin_bit_cast(_Float16, (uint16_t)(v & 0xffffu));
-  }
-  static __device__ __forceinline__ float hi(raw v) {
-    return (float)__builtin_bit_cast(_Float16, (uint16_t)(v >> 16));
-  }
-};
-template <> struct Pair<float> {
-  typedef float2 raw;
-  static __device__ __forceinline__ raw load(const float* p) {
-    return *reinterpret_cast<const float2*>(p);
-  }
-  static __device__ __forceinline__ float lo(raw v) { return v.x; }
-  static __device__ __forceinline__ float hi(raw v) { return v.y; }
-};
 
 template <typename XT>
 __global__ __launch_bounds__(256) void fp16_state_kernel(
@@ -65,11 +43,13 @@ __global__ __launch_bounds__(256) void fp16_state_kernel(
   const size_t HP = (size_t)H * kP;
 
   const int pp = t & 31, jb = t >> 5, p0 = 2 * pp;
-  typename Pair<XT>::raw xr[32];
+  typename fp16::Pair<XT>::raw xr[32];
   {
-    const XT* xb = x + (tok0 + (size_t)jb * 32) * HP + (size_t)h * kP + p0;
+    const __amdgpu_buffer_rsrc_t xrs = uniform_rsrc(x + tok0 * HP + (size_t)h * kP);
+    const uint32_t xo = (uint32_t)((jb * 32 * HP + p0) * sizeof(XT));
 #pragma unroll
-    for (int r = 0; r < 32; ++r) xr[r] = Pair<XT>::load(xb + (size_t)r * HP);
+    for (int r = 0; r < 32; ++r)
+      xr[r] = fp16::Pair<XT>::load(xrs, xo, (uint32_t)(r * HP * sizeof(XT)));
   }
 
   float dtv = dt[(tok0 + t) * H + h];
@@ -90,14 +70,8 @@ __global__ __launch_bounds__(256) void fp16_state_kernel(
     for (int r2 = 0; r2 < 16; ++r2) {
       const int r = 2 * r2;
       const float l0 = s_lut[jb * 32 + r], l1 = s_lut[jb * 32 + r + 1];
-      const _Float16 a0 = (_Float16)(l0 * Pair<XT>::lo(xr[r]));
-      const _Float16 a1 = (_Float16)(l1 * Pair<XT>::lo(xr[r + 1]));
-      const _Float16 c0 = (_Float16)(l0 * Pair<XT>::hi(xr[r]));
-      const _Float16 c1 = (_Float16)(l1 * Pair<XT>::hi(xr[r + 1]));
-      w0[r2] = (uint32_t)__builtin_bit_cast(uint16_t, a0) |
-               ((uint32_t)__builtin_bit_cast(uint16_t, a1) << 16);
-      w1[r2] = (uint32_t)__builtin_bit_cast(uint16_t, c0) |
-               ((uint32_t)__builtin_bit_cast(uint16_t, c1) << 16);
+      w0[r2] = fp16::Pair<XT>::lut_lo(l0, xr[r], l1, xr[r + 1]);
+      w1[r2] = fp16::Pair<XT>::lut_hi(l0, xr[r], l1, xr[r + 1]);
     }
     uint8_t* r0 = s_x + p0 * kXS + jb * 64;
     uint8_t* r1 = r0 + kXS;

@@ -3,19 +3,25 @@
 // chunk states never go through memory.
 //   per chunk  P_in[c] = fp16(P) out, ChunkScan1's operand (frag::pk16_offset)
 //              dt, cs, LUT as in ChunkState; X~^T = fp16(LUT x)^T in LDS
-//              P <- exp(cs_last) P + B^T X~
+//              P <- fma(exp(cs_last), P, S), S = B^T X~ summed from zero
+// with the bits of ChunkState and StatePassing: a sequence's result does not depend on how many
+// others share the call.
 // A sequence's chunks are serial here, so it takes enough sequences to fill the GPU, and a chunk
 // must take no longer than its bytes.  Vector loads complete in order, so the two streams are
 // split over the waves: waves 0 .. 3 load x two chunks ahead and prepare X~ of chunk c + 1 (one
 // token per thread for its ChunkCumsum) while waves 4 .. 7, each one 32-wide n-tile of the state
-// for all channels, multiply chunk c with B^T fragments requested a chunk ahead.
+// for all channels, multiply chunk c with B^T fragments requested 12 K-steps ahead.
+// Registers: state 32, S 32, fragments 48 of the 128 that two workgroups per CU leave (14 K-steps
+// ahead spill).  S is rounded into P after the next scan barrier, off the chain: whole layer of
+// 128, 256, 257 and 320 sequences of 16 chunks 88.8, 156, 171 and 208 us, against 87.2, 156, 172
+// and 207 with the products added straight into P (other roundings).
 //
 // 2.7B-shaped layer, 320 sequences of 16 chunks: 100 us for the 80 + 41 us of ChunkState and
 // StatePassing (252 instead of 588 MB), and ChunkScan after it 109 instead of 130 us (x is still
 // in the Infinity Cache).  What bounds it: the chain of a chunk (softplus, scan, LUT, X~, with two
 // barriers; a third one for X~ cost 6 to 20 %: 128, 192, 256 and 320 sequences of 16 chunks 53.6,
 // 55.6, 62.0 and 107 us, now 42.6, 48.0, 55.6 and 99.8), beside a second workgroup on the same CU:
-// 257 sequences take what 512 do (101 us).  32 four-byte loads per thread and chunk stalled on
+// the walk of 257 sequences takes what that of 512 does (101 us).  32 four-byte loads per thread and chunk stalled on
 // the 63 a wave can have counted, so x comes in 16-byte runs.
 #include "common.hpp"
 #include "fp16_rows.hpp"
@@ -98,15 +104,19 @@ __global__ __launch_bounds__(kThreads, 4) void fp16_walk_kernel(
         for (int i = 0; i < kV; ++i)
           xv[r * kV + i] = buf_load16(xrs, xo + 16 * i, (uint32_t)(r * HP * sizeof(XT)));
     };
-    // channel i of token r
-    auto xval = [](const uint4 (&xv)[8 * kV], int r, int i) {
+    // X~ of channel i of tokens r and r + 1
+    auto lut_x = [](const uint4 (&xv)[8 * kV], int r, int i, float l0, float l1) {
+      auto word = [&](int row, int k) {
+        const uint4 v = xv[row];
+        return k == 0 ? v.x : k == 1 ? v.y : k == 2 ? v.z : v.w;
+      };
       if constexpr (kV == 1) {
-        const uint32_t w = i < 2 ? xv[r].x : i < 4 ? xv[r].y : i < 6 ? xv[r].z : xv[r].w;
-        return (float)__builtin_bit_cast(_Float16, (uint16_t)((i & 1) ? (w >> 16) : (w & 0xffffu)));
+        const uint32_t w0 = word(r, i >> 1), w1 = word(r + 1, i >> 1);
+        return (i & 1) ? lut_x2<1>(l0, w0, l1, w1) : lut_x2<0>(l0, w0, l1, w1);
       } else {
-        const uint4 v = xv[2 * r + (i >> 2)];
-        const int k = i & 3;
-        return __uint_as_float(k == 0 ? v.x : k == 1 ? v.y : k == 2 ? v.z : v.w);
+        const int k = i & 3, q = i >> 2;
+        return lut_x2(l0, __uint_as_float(word(2 * r + q, k)), l1,
+                      __uint_as_float(word(2 * r + 2 + q, k)));
       }
     };
     // chunk cc: its register set becomes X~ in LDS, then takes chunk cc + kAhead
@@ -146,7 +156,7 @@ __global__ __launch_bounds__(kThreads, 4) void fp16_walk_kernel(
         uint32_t w[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          w[u] = pack_h2(lut[2 * u] * xval(xv, 2 * u, i), lut[2 * u + 1] * xval(xv, 2 * u + 1, i));
+          w[u] = lut_x(xv, 2 * u, i, lut[2 * u], lut[2 * u + 1]);
         *reinterpret_cast<uint4*>(xs + xs_offset(8 * ch + i, tg)) =
             make_uint4(w[0], w[1], w[2], w[3]);
       }
@@ -178,16 +188,16 @@ __global__ __launch_bounds__(kThreads, 4) void fp16_walk_kernel(
         P1[4 * q] = f1.x; P1[4 * q + 1] = f1.y; P1[4 * q + 2] = f1.z; P1[4 * q + 3] = f1.w;
       }
     }
-    constexpr int kS = kQ / 16;
+    constexpr int kS = kQ / 16, kF = 12;  // K-steps of a chunk; B^T fragments in flight
     auto b_rsrc = [&](int cc) {   // the last chunk's again past the end
       const size_t bc = (size_t)b * nc + (cc < nc ? cc : nc - 1);
       return uniform_rsrc(bT_frag + (bc * G + g) * (size_t)kN * kQ + (size_t)nt * kS * 512);
     };
-    uint4 f[kS];
+    uint4 f[kF];
     {
       const __amdgpu_buffer_rsrc_t brs = b_rsrc(0);
 #pragma unroll
-      for (int ks = 0; ks < kS; ++ks) f[ks] = buf_load16(brs, lane16, 1024 * ks);
+      for (int ks = 0; ks < kF; ++ks) f[ks] = buf_load16(brs, lane16, 1024 * ks);
     }
     auto pass_scan = [&]() {
       __syncthreads();
@@ -208,29 +218,36 @@ __global__ __launch_bounds__(kThreads, 4) void fp16_walk_kernel(
       };
       put(P0, dst);
       put(P1, dst + (kN / 16) * 512);
-      const float d = sm.decay[c & 1];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        P0[r] *= d;
-        P1[r] *= d;
-      }
       __syncthreads();   // LUT of chunk c + 1
-      const __amdgpu_buffer_rsrc_t brs = b_rsrc(c + 1);
+      const __amdgpu_buffer_rsrc_t bcur = b_rsrc(c), brs = b_rsrc(c + 1);
       const uint8_t* xs = sm.xs[c & 1];
       // opaque per chunk: its addresses are formed here and not held across the loop
       int l = lane;
       asm volatile("" : "+v"(l));
       const int pc = l & 31, half = l >> 5;
+      // S on its own from zero, then one rounding into P, as ChunkState and StatePassing form them
+      // (bit-equal to those)
+      v16f S0, S1;
 #pragma unroll
       for (int ks = 0; ks < kS; ++ks) {
-        const v8h bf = __builtin_bit_cast(v8h, f[ks]);
+        const v8h bf = __builtin_bit_cast(v8h, f[ks < kF ? ks : ks - kF]);
         const v8h a0 = *reinterpret_cast<const v8h*>(xs + xs_offset(pc, 2 * ks + half));
         const v8h a1 = *reinterpret_cast<const v8h*>(xs + xs_offset(32 + pc, 2 * ks + half));
-        P0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf, a0, P0, 0, 0, 0);
-        P1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf, a1, P1, 0, 0, 0);
-        f[ks] = buf_load16(brs, lane16, 1024 * ks);
+        S0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf, a0, ks ? S0 : (v16f){}, 0, 0, 0);
+        S1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf, a1, ks ? S1 : (v16f){}, 0, 0, 0);
+        // the slot's next fragment: of this chunk's end, or of the next chunk
+        if (ks < kS - kF) f[ks] = buf_load16(bcur, lane16, 1024 * (ks + kF));
+        else f[ks < kF ? ks : ks - kF] = buf_load16(brs, lane16, 1024 * (ks < kF ? ks : ks - kF));
       }
+      // (one value per workgroup; read here, as the producers may write it after the next barrier)
+      const float d = __uint_as_float(
+          __builtin_amdgcn_readfirstlane((int)__float_as_uint(sm.decay[c & 1])));
       if (c + 1 < nc) pass_scan();   // chunk c + 2: X~ of chunk c + 1 is there
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        P0[r] = __builtin_fmaf(d, P0[r], S0[r]);
+        P1[r] = __builtin_fmaf(d, P1[r], S1[r]);
+      }
     }
     if (final_state) {
       int l = threadIdx.x & 63;

@@ -154,6 +154,28 @@ def test_fp16_walk_matches_oracle(torch, ssdi8, batch, seqlen, nheads, ngroups, 
 
 
 @pytest.mark.parametrize("dtype", ["fp16", "fp32"])
+@pytest.mark.parametrize("chunks", [1, 2, 9, 33])
+def test_fp16_walk_equals_separate_kernels(torch, ssdi8, chunks, dtype):
+    """A sequence's result does not depend on how many others share the call: 2 x 48 sequences
+    (walked) and each 48 on their own (the separate kernels) agree bit for bit, very slow heads and
+    an inexact scan among them."""
+    torch.manual_seed(chunks)
+    dt_ = torch.float16 if dtype == "fp16" else torch.float32
+    B, L, H = 2, chunks * 256, 48
+    x, Bt, Ct = (torch.randn(B, L, *s, device="cuda").to(dt_)
+                 for s in ((H, 64), (1, 128), (1, 128)))
+    dt = torch.randn(B, L, H, device="cuda") * 0.5 - 2
+    dt[1, :256:3, 7] = -18.0
+    A = -torch.exp(torch.rand(H, device="cuda") * 7 - 7)
+    init = torch.randn(B, H, 64, 128, device="cuda")
+    run = lambda s: ssdi8.ssd_chunk_scan_fp16(x[s], dt[s], A, Bt[s], Ct[s], init_state=init[s],
+                                              y_dtype=torch.float32)
+    both, one = run(slice(0, 2)), [run(slice(b, b + 1)) for b in range(B)]
+    for k in ("final_state", "y"):
+        assert torch.equal(both[k], torch.cat([o[k] for o in one])), k
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "fp32"])
 @pytest.mark.parametrize("value,token", [(float("inf"), 3), (float("nan"), 70),
                                          (float("-inf"), 255)])
 def test_fp16_scan_non_finite_x(torch, ssdi8, dtype, value, token):
