@@ -18,6 +18,7 @@ decltype(&ssdi8_quantize_act) g_quantize = nullptr;
 decltype(&ssdi8_ssd_workspace_size) g_workspace_size = nullptr;
 decltype(&ssdi8_ssd_chunk_scan) g_scan = nullptr;
 decltype(&ssdi8_decode_step) g_decode = nullptr;
+c10::DeviceType g_device = c10::DeviceType::CUDA;   // where its tensors live
 
 // Thrown (and caught at the entry) for arguments that belong to the Python path.
 struct NotPlain {};
@@ -31,7 +32,8 @@ struct Shape {
 const at::Tensor& any_tensor(PyObject* o) {
   if (!THPVariable_CheckExact(o)) throw NotPlain();
   const at::Tensor& t = THPVariable_Unpack(o);
-  if (!t.defined() || t.layout() != at::kStrided || !t.is_cuda() || !t.is_contiguous())
+  if (!t.defined() || t.layout() != at::kStrided || t.device().type() != g_device ||
+      !t.is_contiguous())
     throw NotPlain();
   return t;
 }
@@ -66,12 +68,14 @@ int64_t integer(PyObject* o) {
 at::Tensor empty(const at::Tensor& like, at::ScalarType dtype, std::initializer_list<int64_t> s) {
   return at::empty(s, like.options().dtype(dtype).requires_grad(false));
 }
+// The library call without the GIL, which is back also where f throws.  Tensors are looked at before:
+// data_ptr() throws for one without storage (a functorch wrapper).
 template <typename F> ssdi8_status released(F&& f) {
-  ssdi8_status st;
-  Py_BEGIN_ALLOW_THREADS
-  st = f();
-  Py_END_ALLOW_THREADS
-  return st;
+  struct NoGil {
+    PyThreadState* state = PyEval_SaveThread();
+    ~NoGil() { PyEval_RestoreThread(state); }
+  } no_gil;
+  return f();
 }
 template <typename F> PyObject* guarded(F&& f) {
   try {
@@ -83,10 +87,12 @@ template <typename F> PyObject* guarded(F&& f) {
 }
 void* stream_of(PyObject* o) { return reinterpret_cast<void*>((uintptr_t)integer(o)); }
 
-// bind(quantize, workspace_size, scan, decode): the library's addresses
+// bind(quantize, workspace_size, scan, decode, device): the library's addresses and the type of the
+// device its tensors live on
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  if (n != 4) {
-    PyErr_SetString(PyExc_TypeError, "bind takes 4 addresses");
+  const char* device = n == 5 ? PyUnicode_AsUTF8(a[4]) : nullptr;
+  if (!device) {
+    if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "bind takes 4 addresses and a device");
     return nullptr;
   }
   void* p[4];
@@ -101,6 +107,12 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   g_workspace_size = reinterpret_cast<decltype(g_workspace_size)>(p[1]);
   g_scan = reinterpret_cast<decltype(g_scan)>(p[2]);
   g_decode = reinterpret_cast<decltype(g_decode)>(p[3]);
+  try {
+    g_device = c10::Device(device).type();
+  } catch (const std::exception& e) {
+    PyErr_SetString(PyExc_ValueError, e.what());
+    return nullptr;
+  }
   Py_RETURN_NONE;
 }
 
@@ -127,10 +139,11 @@ PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
     at::Tensor out = a[3] == Py_None ? empty(src, at::kChar, {b, l, k, m}) : tensor(a[3], at::kChar);
     if (!has_shape(out, {b, l, k, m})) throw NotPlain();
     void* st = stream_of(a[4]);
+    const void* from = src.data_ptr();
+    float* steps = static_cast<float*>(scale.data_ptr());
+    int8_t* to = static_cast<int8_t*>(out.data_ptr());
     const ssdi8_status s = released([&] {
-      return g_quantize(src.data_ptr(), code, b, l, k, m, gran,
-                        static_cast<float*>(scale.data_ptr()), dynamic ? 1 : 0,
-                        static_cast<int8_t*>(out.data_ptr()), st);
+      return g_quantize(from, code, b, l, k, m, gran, steps, dynamic ? 1 : 0, to, st);
     });
     return Py_BuildValue("(iNN)", (int)s, THPVariable_Wrap(out), THPVariable_Wrap(scale));
   });
@@ -261,7 +274,7 @@ PyObject* decode(PyObject*, PyObject* const* o, Py_ssize_t n) {
 
 #define SSDI8_FAST(f) reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(f)), METH_FASTCALL
 PyMethodDef methods[] = {
-    {"bind", SSDI8_FAST(bind), "bind(quantize_act, ssd_workspace_size, ssd_chunk_scan, decode_step)"},
+    {"bind", SSDI8_FAST(bind), "bind(quantize_act, ssd_workspace_size, ssd_chunk_scan, decode_step, device)"},
     {"quantize", SSDI8_FAST(quantize), "ssdi8_quantize_act"},
     {"scan", SSDI8_FAST(scan), "ssdi8_ssd_chunk_scan"},
     {"decode", SSDI8_FAST(decode), "ssdi8_decode_step"},

@@ -137,7 +137,7 @@ def lib() -> ctypes.CDLL:
     addr = lambda f: ctypes.cast(f, ctypes.c_void_p).value
     from . import _binding
     _binding.bind(addr(L.ssdi8_quantize_act), addr(L.ssdi8_ssd_workspace_size),
-                  addr(L.ssdi8_ssd_chunk_scan), addr(L.ssdi8_decode_step))
+                  addr(L.ssdi8_ssd_chunk_scan), addr(L.ssdi8_decode_step), "cuda")
     _native = _binding
     _lib = L
     return L
