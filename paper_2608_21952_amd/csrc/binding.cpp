@@ -65,16 +65,20 @@ int64_t integer(PyObject* o) {
   if (v == -1 && PyErr_Occurred()) throw NotPlain();
   return v;
 }
+// No GIL while this lives; it is back also where an exception leaves.
+struct NoGil {
+  PyThreadState* state = PyEval_SaveThread();
+  ~NoGil() { PyEval_RestoreThread(state); }
+};
+// An allocation may wait for the device, and the device for a host callback that takes the GIL.
 at::Tensor empty(const at::Tensor& like, at::ScalarType dtype, std::initializer_list<int64_t> s) {
+  NoGil no_gil;
   return at::empty(s, like.options().dtype(dtype).requires_grad(false));
 }
-// The library call without the GIL, which is back also where f throws.  Tensors are looked at before:
-// data_ptr() throws for one without storage (a functorch wrapper).
+// The library call.  Tensors are looked at before: data_ptr() throws for one without storage (a
+// functorch wrapper).
 template <typename F> ssdi8_status released(F&& f) {
-  struct NoGil {
-    PyThreadState* state = PyEval_SaveThread();
-    ~NoGil() { PyEval_RestoreThread(state); }
-  } no_gil;
+  NoGil no_gil;
   return f();
 }
 template <typename F> PyObject* guarded(F&& f) {
