@@ -164,15 +164,18 @@ __device__ __forceinline__ void row_block(int jt, int lane, const Tables& T, con
     }
   }
   // Leading off-diagonal blocks whose every weight rounds to an fp16 zero are skipped: |W| <=
-  // max |CB| max |u| R (e_j <= 1), and below 2^-26 (half the smallest fp16 subnormal is 2^-25) it
-  // is zero.
+  // max |CB| max |u| R e_j, and below 2^-26 (half the smallest fp16 subnormal is 2^-25) it is zero.
+  // e_j <= 1 where no row of the block lies above cs at the block's start; a block in which one
+  // does (or is NaN; dt or A outside the method's signs) skips nothing.
   const uint32_t cbrow = frag::cb_block(jt, 0) * 4096;
   const bool diag_fast =
       __builtin_amdgcn_readfirstlane((int)(T.csr[jt * 32 + 31] >= -kDiagSpan)) != 0;
   int it0 = jt;
   {
     const int k = lane & 7;
-    const bool live = k < jt && !(cbm * T.umax[k] * T.R[jt ? jt - 1 : 0][k] < 0x1p-26f);
+    const bool rises = __ballot(!(csrj <= 0.0f)) != 0;
+    const bool live =
+        k < jt && (rises || !(cbm * T.umax[k] * T.R[jt ? jt - 1 : 0][k] < 0x1p-26f));
     const uint32_t lv = (uint32_t)__ballot(live) & 0xffu;
     if (lv) it0 = (int)__builtin_ctz(lv);
     it0 = __builtin_amdgcn_readfirstlane(it0);

@@ -194,3 +194,31 @@ def test_fp16_scan_non_finite_x(torch, ssdi8, dtype, value, token):
     assert not bool(fin[0, token:, :, 5].any())
     fin[..., 5] = True
     assert bool(fin.all())
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "fp32"])
+def test_fp16_scan_decay_that_rises_again(torch, ssdi8, dtype):
+    """dt of both signs without the softplus: cs falls by 32 over one block of 32 tokens and rises by
+    32 over the next, so weights that are zero at that block's first row are of order one at its
+    last.  The tokens in between have B = 0 (their weights would leave the fp16 range).  Against 64
+    bits: weights rounded to fp16 (2^-11 relative each), twice that for the fp32 factors of the
+    decay, of the sum of |W x|."""
+    torch.manual_seed(9)
+    dt_ = torch.float16 if dtype == "fp16" else torch.float32
+    B, L, H = 1, 256, 3
+    x, Bt, Ct = (torch.randn(B, L, *s, device="cuda").half().to(dt_)
+                 for s in ((H, 64), (1, 128), (1, 128)))
+    Bt[:, 32:96] = 0
+    dt = torch.full((B, L, H), 0.02, device="cuda")
+    dt[:, :32], dt[:, 32:64], dt[:, 64:96] = 0.05, 1.0, -1.0
+    A = torch.tensor([-1.0, -0.9, -1.1], device="cuda")
+    y = ssdi8.ssd_chunk_scan_fp16(x, dt, A, Bt, Ct, dt_softplus=False,
+                                  y_dtype=torch.float32)["y"].double()
+    cs = torch.cumsum((dt * A).double(), 1)[0].T.contiguous()                  # (H, L)
+    cb = (Ct[0, :, 0].double() @ Bt[0, :, 0].double().T.contiguous()).tril()
+    W = cb * dt[0].T.double()[:, None] * torch.exp((cs[:, :, None] - cs[:, None]).tril())
+    xh = x[0].double().permute(1, 0, 2).contiguous()
+    ref = (W @ xh).permute(1, 0, 2)
+    bound = (W.abs() @ xh.abs()).permute(1, 0, 2) * 2.0 ** -10 + 2.0 ** -20
+    assert bool(((y[0] - ref).abs() <= bound).all())
+    assert float(ref[88:96].abs().max()) > 0.1    # the rows in question are not small
