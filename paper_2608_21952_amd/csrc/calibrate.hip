@@ -181,8 +181,8 @@ __global__ __launch_bounds__(256) void calib_pass_kernel(const float* __restrict
 
 // ---- steps from the absolute maxima: block b < nsteps the x and state steps of 256 channels, the
 //      others the C.B^T step of one group each, from the maxima of its 36 blocks per chunk
-//      (cb_max [ncg, 36], chunk-groups of a group G apart; one atomic per block on one word per
-//      group took ChunkBMM from 7 to 19 us)
+//      (cb_max [ncg, 36], chunk-groups of a group G apart, the sign bit for NaNs left out; one
+//      atomic per block on one word per group took ChunkBMM from 7 to 19 us)
 __global__ __launch_bounds__(256) void calib_steps_kernel(
     const uint32_t* __restrict__ xs_amax, const uint32_t* __restrict__ s_amax,
     const float* __restrict__ cb_max, float* __restrict__ aXs, float* __restrict__ aS,
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(256) void calib_steps_kernel(
     float m = 0.0f;
     for (int i = threadIdx.x; i < n; i += 256) {
       const int c = i / frag::kCbBlocks, k = i - c * frag::kCbBlocks;
-      m = __builtin_fmaxf(m, cb_max[((size_t)c * G + g) * frag::kCbBlocks + k]);
+      m = __builtin_fmaxf(m, __builtin_fabsf(cb_max[((size_t)c * G + g) * frag::kCbBlocks + k]));
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, o, 64));

@@ -144,8 +144,9 @@ __global__ __launch_bounds__(256) void fp16_bmm_kernel(const T* __restrict__ C,
                                           1024 + lane * 4);
 #pragma unroll
   for (int u = 0; u < 4; ++u) out[64 * u] = o[u];
-  // absolute maximum of the tile's causal entries (the masked ones were staged as 0): ChunkScan2
-  // skips blocks by it (a NaN counts as infinite there), and calibration takes its step from it
+  // absolute maximum of the tile's causal entries (the masked ones were staged as 0), NaNs left out,
+  // its sign bit set where there is one: ChunkScan2 skips blocks by it (a NaN counts as infinite
+  // there), and calibration takes its step from it (a NaN does not count)
   float m = 0.0f;
   bool nan = false;
 #pragma unroll
@@ -160,7 +161,7 @@ __global__ __launch_bounds__(256) void fp16_bmm_kernel(const T* __restrict__ C,
   for (int off = 32; off >= 1; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off, 64));
   const bool any_nan = __ballot(nan) != 0;
   if (lane == 0)
-    cb_max[cg * frag::kCbBlocks + frag::cb_block(jt, it)] = any_nan ? __builtin_inff() : m;
+    cb_max[cg * frag::kCbBlocks + frag::cb_block(jt, it)] = any_nan ? -m : m;
 }
 
 }  // namespace

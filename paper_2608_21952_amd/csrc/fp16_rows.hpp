@@ -117,7 +117,8 @@ __device__ __forceinline__ void build_tables(Tables& T, int t, float dtv, double
   }
 }
 
-// The maximum this lane contributes to row block jt's skip test (lane & 7 = block), for row_block.
+// The maximum this lane contributes to row block jt's skip test (lane & 7 = block), for row_block:
+// its sign bit says that the block holds a NaN.
 __device__ __forceinline__ float block_max(const float* cb_max_cg, int jt, int lane) {
   const int k = lane & 7;
   return cb_max_cg[frag::cb_block(jt, 0) + (k < jt ? k : 0)];
@@ -175,7 +176,8 @@ __device__ __forceinline__ void row_block(int jt, int lane, const Tables& T, con
     const int k = lane & 7;
     const bool rises = __ballot(!(csrj <= 0.0f)) != 0;
     const bool live =
-        k < jt && (rises || !(cbm * T.umax[k] * T.R[jt ? jt - 1 : 0][k] < 0x1p-26f));
+        k < jt && (rises || (int)__float_as_uint(cbm) < 0 ||
+                   !(cbm * T.umax[k] * T.R[jt ? jt - 1 : 0][k] < 0x1p-26f));
     const uint32_t lv = (uint32_t)__ballot(live) & 0xffu;
     if (lv) it0 = (int)__builtin_ctz(lv);
     it0 = __builtin_amdgcn_readfirstlane(it0);

@@ -182,3 +182,22 @@ def test_correction_from_channel_sums(torch, ssdi8, B, L, H, G, dtype):
             for t in (Ct, Bt))
     cb = (c @ b.transpose(3, 4).contiguous()).tril().abs().amax((0, 1, 3, 4)) / 127.0
     assert bool(((s["alpha_CB"] - cb).abs() <= 1e-5 * cb).all())
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "fp32"])
+def test_nan_does_not_count_in_the_steps_of_b_and_c(torch, ssdi8, dtype):
+    """A token whose B or C is zero but for a NaN leaves the steps of B, C and C B^T as a zero row
+    does: the maxima leave NaNs out."""
+    torch.manual_seed(8)
+    dt_ = torch.float16 if dtype == "fp16" else torch.float32
+    B, L, H, G = 1, 512, 4, 2
+    x = torch.randn(B, L, H, 64, device="cuda").to(dt_)
+    dt, A = torch.randn(B, L, H, device="cuda") - 2, -torch.rand(H, device="cuda")
+    Bt, Ct = (torch.randn(B, L, G, 128, device="cuda").to(dt_) for _ in range(2))
+    Bt[0, 300, 0], Ct[0, 40, 1] = 0, 0
+    names = ("alpha_B", "alpha_C", "alpha_CB")
+    zero = ssdi8.calibrate(x, dt, A, Bt, Ct)
+    Bt[0, 300, 0, 5], Ct[0, 40, 1, 99] = float("nan"), float("nan")
+    nan = ssdi8.calibrate(x, dt, A, Bt, Ct)
+    for k in names:
+        assert torch.equal(nan[k], zero[k]), (k, nan[k], zero[k])

@@ -222,3 +222,14 @@ def test_fp16_scan_decay_that_rises_again(torch, ssdi8, dtype):
     bound = (W.abs() @ xh.abs()).permute(1, 0, 2) * 2.0 ** -10 + 2.0 ** -20
     assert bool(((y[0] - ref).abs() <= bound).all())
     assert float(ref[88:96].abs().max()) > 0.1    # the rows in question are not small
+
+
+def test_fp16_scan_nan_in_b(torch, ssdi8):
+    """A NaN in B reaches every later row of its chunk, also through weights that decay to zero."""
+    torch.manual_seed(4)
+    B, L, H = 1, 256, 2
+    x, Bt, Ct = (torch.randn(B, L, *s, device="cuda").half() for s in ((H, 64), (1, 128), (1, 128)))
+    Bt[0, 3, 0, 77] = float("nan")
+    y = ssdi8.ssd_chunk_scan_fp16(x, torch.zeros(B, L, H, device="cuda"),
+                                  torch.tensor([-200.0, -0.1], device="cuda"), Bt, Ct)["y"]
+    assert bool(torch.isnan(y[0, 3:]).all()) and bool(torch.isfinite(y[0, :3]).all())
