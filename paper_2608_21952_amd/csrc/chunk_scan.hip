@@ -311,7 +311,21 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
       *reinterpret_cast<uint4*>(r1 + 16 * q) = make_uint4(bb[0], bb[1], bb[2], bb[3]);
     }
   };
+  // ChunkScan1's operand fragments of P_in (frag.hpp: 1 KB per fragment, this lane's 16 bytes at
+  // lane * 16).  The separate kernel requests them here, behind x and before the waits for it: few
+  // workgroups have nothing else to hide their latency (24 sequences of 8 chunks: this kernel's layer
+  // 27.7 -> 27.0 us, fp32 x 36.6 -> 35.6 us; 80 heads of 64 chunks in fp32 370 -> 368 us).
+  const uint32_t lane16 = lane * 16;
+  const __amdgpu_buffer_rsrc_t prs =
+      buffer_rsrc(pin + (((size_t)b * nc + c) * H + h) * (size_t)kP * kN);
+  auto frag_of = [&](__amdgpu_buffer_rsrc_t r, uint32_t o) {
+    return __builtin_bit_cast(v4i, buf_load16(r, lane16, o));
+  };
+  v4i pf[2 * kN / 32];
   if constexpr (!kFused) {
+#pragma unroll
+    for (int i = 0; i < 2 * kN / 32; ++i) pf[i] = frag_of(prs, 1024 * i);
+    __builtin_amdgcn_sched_barrier(0);
     stage_xT();
   } else {
     // single pass: X_q^T [p][j] (int8, Eq. 7) first, in the bytes x^T takes later: each x
@@ -641,12 +655,8 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
   // lane owns one token row j and runs of 4 consecutive channels: the epilogue needs one row
   // factor per lane and moves 8-byte vectors.  Lane l: j = 32 jt + (l % 32); accumulator
   // register r holds channel p = 32 pt + 8 (r / 4) + 4 (l / 32) + r % 4.
-  // operand fragments (frag.hpp): 1 KB per fragment, this lane's 16 bytes at lane * 16
   const int pc = lane & 31, half = lane >> 5;
   const size_t cg = ((size_t)b * nc + c) * G + g;
-  const uint32_t lane16 = lane * 16;
-  const __amdgpu_buffer_rsrc_t prs =
-      buffer_rsrc(pin + (((size_t)b * nc + c) * H + h) * (size_t)kP * kN);
   const __amdgpu_buffer_rsrc_t cbrs = buffer_rsrc(cbq + cg * (size_t)frag::kCbChunkBytes);
   const __amdgpu_buffer_rsrc_t cqrs = buffer_rsrc(cq_frag + cg * (size_t)kQ * kN);
   const float Dh = Dv ? Dv[h] : 0.0f;
@@ -833,14 +843,11 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
   v16i ia0, ia1, ib0, ib1;
   {
     const uint32_t ca = jta * (kN / 32) * 1024, cb = jtb * (kN / 32) * 1024;
-    constexpr uint32_t p1row = (kN / 32) * 1024;
-    auto frag_of = [&](__amdgpu_buffer_rsrc_t r, uint32_t o) {
-      return __builtin_bit_cast(v4i, buf_load16(r, lane16, o));
-    };
+    auto pin_frag = [&](int i) { return kFused ? frag_of(prs, 1024 * i) : pf[i]; };
     if (need_b) {
 #pragma unroll
       for (int ks = 0; ks < kN / 32; ++ks) {
-        const v4i p0 = frag_of(prs, 1024 * ks), p1 = frag_of(prs, p1row + 1024 * ks);
+        const v4i p0 = pin_frag(ks), p1 = pin_frag(kN / 32 + ks);
         const v4i fa = frag_of(cqrs, ca + 1024 * ks), fb = frag_of(cqrs, cb + 1024 * ks);
         ia0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p0, fa, ks ? ia0 : (v16i){}, 0, 0, 0);
         ia1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p1, fa, ks ? ia1 : (v16i){}, 0, 0, 0);
@@ -850,7 +857,7 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
     } else if (need_a) {
 #pragma unroll
       for (int ks = 0; ks < kN / 32; ++ks) {
-        const v4i p0 = frag_of(prs, 1024 * ks), p1 = frag_of(prs, p1row + 1024 * ks);
+        const v4i p0 = pin_frag(ks), p1 = pin_frag(kN / 32 + ks);
         const v4i fa = frag_of(cqrs, ca + 1024 * ks);
         ia0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p0, fa, ks ? ia0 : (v16i){}, 0, 0, 0);
         ia1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p1, fa, ks ? ia1 : (v16i){}, 0, 0, 0);
