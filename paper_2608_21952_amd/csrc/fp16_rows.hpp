@@ -295,29 +295,45 @@ __device__ __forceinline__ void rows_out(const uint8_t* s_y, __amdgpu_buffer_rsr
 }
 static_assert(kP * kXTS >= kQ * kP * 2, "the output stages reuse the x^T bytes");
 
+// v of lane l ^ kXor, kXor < 32: a swizzle, which needs no lane address in a register.
+template <int kXor> __device__ __forceinline__ double swizzle_xor_f64(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_swizzle((int)(uint32_t)u, (kXor << 10) | 0x1f);
+  const uint32_t hi =
+      (uint32_t)__builtin_amdgcn_ds_swizzle((int)(uint32_t)(u >> 32), (kXor << 10) | 0x1f);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// One exchange of a reduce-scatter: of values 0 .. 2 kO - 1 the lanes with bit kO keep the upper half.
+template <int kO> __device__ __forceinline__ void exchange_half(double (&v)[16], int lane) {
+  const bool up = (lane & kO) != 0;
+#pragma unroll
+  for (int i = 0; i < kO; ++i) {
+    const double keep = up ? v[i + kO] : v[i], send = up ? v[i] : v[i + kO];
+    v[i] = keep + swizzle_xor_f64<kO>(send);
+  }
+}
+
 // Instead of its rows: the fp64 sums over the chunk's 256 tokens of every channel of y, in a fixed
 // order, to out[0 .. 63] (calibration needs only the mean of y; as rows it would be written and
 // read back in fp32).  A lane adds its two rows, then the 32 lanes of a half-wave reduce and
 // scatter in five exchanges, after which lane l % 32 holds register l % 32 of (y0, y1); the four
-// waves add up through LDS (s_sum: 2 KB that nothing else uses any more).
+// waves add up through LDS (s_sum: 2 KB that nothing else uses any more).  By shuffles, whose lane
+// address the compiler formed at the kernel's start and held across it, the FP16 layer's scan
+// spilled two registers.
 __device__ __forceinline__ void channel_sums(double* s_sum, int wv, int lane, const v16f& ya0,
                                              const v16f& ya1, const v16f& yb0, const v16f& yb1,
                                              double* out) {
-  double v[32];
+  double v[16];
+  const bool upper = (lane & 16) != 0;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    v[r] = (double)ya0[r] + (double)yb0[r];
-    v[16 + r] = (double)ya1[r] + (double)yb1[r];
+    const double s0 = (double)ya0[r] + (double)yb0[r], s1 = (double)ya1[r] + (double)yb1[r];
+    v[r] = (upper ? s1 : s0) + swizzle_xor_f64<16>(upper ? s0 : s1);
   }
-#pragma unroll
-  for (int o = 16; o >= 1; o >>= 1) {
-    const bool up = (lane & o) != 0;   // keeps the upper half of the values
-#pragma unroll
-    for (int i = 0; i < o; ++i) {
-      const double keep = up ? v[i + o] : v[i], send = up ? v[i] : v[i + o];
-      v[i] = keep + __shfl_xor(send, o, 64);
-    }
-  }
+  exchange_half<8>(v, lane);
+  exchange_half<4>(v, lane);
+  exchange_half<2>(v, lane);
+  exchange_half<1>(v, lane);
   const int r = lane & 31;
   const int p = 32 * (r >> 4) + 8 * ((r & 15) >> 2) + 4 * (lane >> 5) + (r & 3);
   s_sum[wv * kP + p] = v[0];

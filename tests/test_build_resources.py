@@ -1,8 +1,8 @@
 """Register and LDS budgets of the hot kernels, from the compiler's resource-usage remarks
 (gfx950, the library's own flags): no VGPR spills and no scratch memory at all (a value
 reloaded from scratch is a vector-memory load, which waits behind every load in flight), and
-the single pass and the separate ChunkScan within four workgroups per CU (at most 128 VGPRs,
-40 KB of LDS).  A few SGPRs may spill into the lanes of a VGPR (v_writelane / v_readlane, no
+the single pass, the separate ChunkScan and the FP16 layer's within four workgroups per CU (at most
+128 VGPRs, 40 KB of LDS).  A few SGPRs may spill into the lanes of a VGPR (v_writelane / v_readlane, no
 memory access): the single pass's instantiations with fp16 output hold 4-6 that way, counted in
 their VGPRs."""
 import os
@@ -39,7 +39,9 @@ pytestmark = pytest.mark.skipif(shutil.which(libbuild.hipcc()) is None and
 
 
 @pytest.mark.parametrize("src", ["chunk_scan.hip", "chunk_bmm.hip", "chunk_state.hip",
-                                 "state_pass.hip", "quantize.hip", "decode.hip"])
+                                 "state_pass.hip", "quantize.hip", "decode.hip",
+                                 "fp16_bmm.hip", "fp16_state.hip", "fp16_scan.hip",
+                                 "fp16_walk.hip", "calibrate.hip"])
 def test_no_register_spills(src):
     res = _resources(src)
     assert res, f"no kernels found in {src}"
@@ -49,7 +51,8 @@ def test_no_register_spills(src):
         assert r.get("SGPRs Spill", 0) <= 8, f"{name}: {r}"
 
 
-def test_chunk_scan_fits_four_workgroups_per_cu():
-    for name, r in _resources("chunk_scan.hip").items():
+@pytest.mark.parametrize("src", ["chunk_scan.hip", "fp16_scan.hip"])
+def test_chunk_scan_fits_four_workgroups_per_cu(src):
+    for name, r in _resources(src).items():
         assert r["VGPRs"] + r.get("AGPRs", 0) <= 128, f"{name}: {r}"
         assert r["LDS Size"] <= 40 * 1024, f"{name}: {r}"
