@@ -153,19 +153,22 @@ def test_correction_is_the_damped_mean_of_the_layer_difference(torch, ssdi8):
                                atol=1e-6 * float(np.abs(before).max()) + 1e-7)
 
 
-@pytest.mark.parametrize("B,L,H,G,dtype", [
-    (1, 256, 3, 3, "fp16"),     # one chunk: one row per layer, the single pass
-    (1, 1280, 5, 1, "fp16"),    # five chunks of few sequences: the separate kernels
-    (3, 768, 6, 2, "fp32"),     # fp32 x, nine rows
-    (2, 1280, 60, 4, "fp16"),   # the speculative single pass, the walked FP16 states
+@pytest.mark.parametrize("B,L,H,G,dtype,single", [
+    (1, 256, 3, 3, "fp16", True),      # one chunk: one row per layer
+    (1, 1280, 5, 1, "fp16", True),     # five chunks of few sequences
+    (1, 1536, 5, 1, "fp16", False),    # six of them: the separate kernels
+    (3, 768, 6, 2, "fp32", False),     # fp32 x, nine rows
+    (2, 1280, 60, 4, "fp16", True),    # the walked FP16 states
+    (4, 1280, 104, 2, "fp16", True),   # more than eight items per CU: no speculative loads
 ])
-def test_correction_from_channel_sums(torch, ssdi8, B, L, H, G, dtype):
+def test_correction_from_channel_sums(torch, ssdi8, B, L, H, G, dtype, single):
     """corr is eta times the mean of the two layers' own fp32 outputs: the kernels sum the same
     fp32 values in fp64, so only the order of those sums (2^-53 of the sum of |y| each) and the
     last rounding to fp32 differ.  alpha_CB is the largest causal entry of fp16 C B^T / 127, summed
     in fp32 here and there: 128 terms, 1e-5 of it."""
     torch.manual_seed(B + L + H)
     dt_ = torch.float16 if dtype == "fp16" else torch.float32
+    assert ssdi8.uses_single_pass(ssdi8.dims(B, L, H, G), dt_) == single
     x = (torch.randn(B, L, H, 64, device="cuda") * 3).to(dt_)
     dt = torch.randn(B, L, H, device="cuda") * 0.5 - 2
     A, D = -torch.exp(torch.rand(H, device="cuda") * 6 - 4), torch.rand(H, device="cuda")
