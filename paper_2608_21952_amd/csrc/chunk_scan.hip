@@ -498,8 +498,11 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
     const uint4 sq1 = make_uint4(sq[1][0], sq[1][1], sq[1][2], sq[1][3]);
     // With Q(Decay) = 0, Eq. 9 gives P_in[c+1] = clamp(S_q[c] + (r >> k)) whatever P_in[c] is:
     // such a chunk publishes P_in[c+1] before it obtains P_in[c], so that its successor finds
-    // an anchor at once (the same integers; its S_q is then never needed by later chunks)
-    const bool early = qd == 0 && c + 1 < nc;
+    // an anchor at once (the same integers; its S_q is then never needed by later chunks).  Not
+    // chunk 0 of a sequence resumed in place: the last chunk, which may find that anchor before
+    // chunk 0 has read the initial state, writes the final state over it
+    const bool in_place = c == 0 && fs.init && fs.init == fs.final_q;
+    const bool early = qd == 0 && c + 1 < nc && !in_place;
     if (early) {
       // r < 2^k (r = 2^(k-1) or 0) makes it S_q[c] itself (codes within +-127)
       const bool same = (fs.radd >> fs.shift) == 0;

@@ -304,3 +304,42 @@ def test_single_pass_few_sequences(torch, ssdi8, batch, nheads, ngroups, nchunks
     assert_equal(one["state_in_q"], ref["pin"], "P_in vs oracle chain")
     assert np.array_equal(one["final_state_q"], ref["final_q"])
     assert_close(one["y"], ref["y64"], "y (few sequences)")
+
+
+@pytest.mark.parametrize("H,nc", [(1, 2), (24, 3), (24, 5), (72, 9)])
+def test_final_state_over_the_initial_state(torch, ssdi8, H, nc):
+    """A caller of the C ABI may resume a sequence in place, final_state_q over init_state_q.  Heads
+    whose Q(Decay) is zero in every chunk publish P_in[1] before they obtain P_in[0], so the last
+    chunk may be done first: chunk 0 has read the initial state by then.  x is zero, so that y is
+    ChunkScan1 of the entering states alone."""
+    say(f"final over initial state H={H} chunks={nc}")
+    torch.manual_seed(nc)
+    L, d = 256 * nc, ssdi8.dims(1, 256 * nc, H, 1)
+    x = torch.zeros(1, L, H, 64, dtype=torch.float16, device="cuda")
+    dt = torch.full((1, L, H), 0.05, device="cuda")
+    A = torch.full((H,), -1.0, device="cuda")       # exp(-12.8) of 128 rounds to 0
+    B, C = (torch.randint(-127, 128, (1, L, 1, 128), dtype=torch.int8, device="cuda") for _ in "BC")
+    o = lambda *sh: torch.full(sh, 0.02, device="cuda")
+    init = torch.randint(-127, 128, (1, H, 64, 128), dtype=torch.int8, device="cuda")
+    step = (o(1), o(1), o(H, 64), o(H, 64), o(1))
+    ref = ssdi8.ssd_chunk_scan(x, dt, A, B, C, *step, dt_softplus=False, init_state_q=init,
+                               path="separate", y_dtype=torch.float32)
+    assert float(ref["y"][:, 0].abs().max()) > 0
+    assert not torch.equal(ref["final_state_q"], init)
+    ws = torch.empty(ssdi8.workspace_size(d), dtype=torch.uint8, device="cuda")
+    to = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for path in (ssdi8.PATHS["single"], ssdi8.PATHS["separate"]):
+        for _ in range(5):
+            state, y = init.clone(), torch.empty_like(ref["y"])
+            a = ssdi8.ScanArgs(
+                x=x.data_ptr(), x_dtype=ssdi8.F16, dt=dt.data_ptr(), A=A.data_ptr(),
+                Bq=B.data_ptr(), Cq=C.data_ptr(), decay_shift=7, shift_round=1,
+                init_state_q=state.data_ptr(), final_state_q=state.data_ptr(), y=y.data_ptr(),
+                y_dtype=ssdi8.F32, workspace=ws.data_ptr(), workspace_bytes=ws.numel(), path=path,
+                hand_off_timeouts=to.data_ptr(),
+                **{k: t.data_ptr() for k, t in zip(("B_scale", "C_scale", "xs_scale", "state_scale",
+                                                    "cb_scale"), step)})
+            assert ssdi8.lib().ssdi8_ssd_chunk_scan(d, a, torch.cuda.current_stream().cuda_stream) == 0
+            torch.cuda.synchronize()
+            assert int(to) == 0
+            assert torch.equal(y, ref["y"]) and torch.equal(state, ref["final_state_q"])
