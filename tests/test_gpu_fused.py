@@ -308,10 +308,10 @@ def test_single_pass_few_sequences(torch, ssdi8, batch, nheads, ngroups, nchunks
 
 @pytest.mark.parametrize("H,nc", [(1, 2), (24, 3), (24, 5), (72, 9)])
 def test_final_state_over_the_initial_state(torch, ssdi8, H, nc):
-    """A caller of the C ABI may resume a sequence in place, final_state_q over init_state_q.  Heads
-    whose Q(Decay) is zero in every chunk publish P_in[1] before they obtain P_in[0], so the last
-    chunk may be done first: chunk 0 has read the initial state by then.  x is zero, so that y is
-    ChunkScan1 of the entering states alone."""
+    """A caller of the C ABI may resume a sequence in place, final_state_q over init_state_q.  Chunks
+    with Q(Decay) zero publish the next entering state before they obtain their own, so the last
+    chunk may be done first, but not before chunk 0 has read the initial state.  x is zero, so that
+    y is ChunkScan1 of the entering states alone."""
     say(f"final over initial state H={H} chunks={nc}")
     torch.manual_seed(nc)
     L, d = 256 * nc, ssdi8.dims(1, 256 * nc, H, 1)

@@ -553,3 +553,29 @@ def test_single_pass_few_chunks(torch, ssdi8, H, nc):
     assert int(to) == 0
     for k in ("y", "final_state_q", "final_state"):
         assert torch.equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("dtype,path", [("half", "separate"), ("half", "single"), ("float", "auto")])
+def test_non_finite_c_step_of_a_token(torch, ssdi8, dtype, path, value):
+    """A token whose C step is not finite has no y, also in heads whose ChunkScan1 is left out there
+    because exp(cs) is zero in fp32; every other token is as without it."""
+    torch.manual_seed(7)
+    H, L, rows = 6, 512, (200, 471)
+    o = lambda *sh: torch.full(sh, 0.02, device="cuda")
+    x = getattr(torch.randn(1, L, H, 64, device="cuda"), dtype)()
+    dt = torch.full((1, L, H), 0.5, device="cuda")
+    A = -torch.tensor([0.01, 0.1, 1.0, 2.0, 4.0, 8.0], device="cuda")   # cs to -1024
+    Bq, Cq = (torch.randint(-127, 128, (1, L, 2, 128), dtype=torch.int8, device="cuda") for _ in "BC")
+    init = torch.randint(-127, 128, (1, H, 64, 128), dtype=torch.int8, device="cuda")
+    run = lambda cs: ssdi8.ssd_chunk_scan(x, dt, A, Bq, Cq, o(2), cs, o(H, 64), o(H, 64), o(2),
+                                          dt_softplus=False, init_state_q=init, path=path)["y"]
+    steps = o(1, L, 2)
+    want = run(steps)
+    assert bool(want.isfinite().all())
+    steps = steps.clone()
+    steps[:, list(rows)] = value
+    got = run(steps)
+    assert not bool(got[:, list(rows)].isfinite().any())
+    keep = [t for t in range(L) if t not in rows]
+    assert torch.equal(got[:, keep], want[:, keep])
