@@ -684,10 +684,8 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
     const size_t orow = (tok0 + jrow) * HP + (size_t)h * kP;
     // a_C(j) exp(cs_j) = a_C(j) exp(cs_j - r_{J-1}) exp(r_{J-1})
     const float eo = ac * ej * exp_r(jt);
-    // what the term adds where Y1 is not needed: 0, or NaN where the C step or exp(cs_j - r_{J-1}) is
-    // not finite (pinned: kept as a product it ties the two seeds together and spills registers)
-    float e0 = 0.0f * eo;
-    asm volatile("" : "+v"(e0));
+    // D where Y1 is not needed: NaN where the term's factor is not finite (0 * it), as the term is
+    const float dj = Dh + 0.0f * eo;
     auto seed = [&](auto with_y1) {
 #pragma unroll
       for (int pt = 0; pt < 2; ++pt) {
@@ -713,11 +711,9 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const int r = 4 * g4 + q;
-            float v = __builtin_fmaf(Dh, xv[q], crv[q]);
+            float v = __builtin_fmaf(decltype(with_y1)::value ? Dh : dj, xv[q], crv[q]);
             if constexpr (decltype(with_y1)::value)
               v = __builtin_fmaf((float)(pt ? yi1[r] : yi0[r]) * eo, asv[q], v);
-            else
-              v += e0;
             if (pt) y1[r] = v;
             else y0[r] = v;
           }
