@@ -21,8 +21,8 @@
 // of both comes first, from one load of P_in (it was loaded per block: 64 instead of 32 KB per
 // workgroup through a texture path that is busy 54-87 % of the time), and its scaled result, with
 // the skip and correction terms, seeds the Scan2 accumulators.  Against Scan2 first and the terms
-// added after it: 2.7B-shaped layer 130.6 -> 125.6 us, 8B-shaped 230.4 -> 223.3 us, 64K-token 564.6
-// -> 551.3 us, 130M-shaped 56.5 -> 56.1 us (whole layers).  Requesting the C_q fragments before the
+// added after it: 2.7B-shaped layer 126.3 -> 123.1 us, 8B-shaped 220.3 -> 214.6 us, 64K-token 541.8
+// -> 529.8 us, 130M-shaped 56.4 -> 55.8 us (whole layers).  Requesting the C_q fragments before the
 // hand-off: +-1 %, not kept.
 // Strong decay removes work exactly: leading off-diagonal blocks whose fp16 weights all round to
 // zero are not formed, and Scan1 is not run for a j-block whose factor exp(cs_j) is zero in fp32.
@@ -311,22 +311,46 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
       *reinterpret_cast<uint4*>(r1 + 16 * q) = make_uint4(bb[0], bb[1], bb[2], bb[3]);
     }
   };
-  // ChunkScan1's operand fragments of P_in (frag.hpp: 1 KB per fragment, this lane's 16 bytes at
-  // lane * 16).  The separate kernel requests them here, behind x and before the waits for it: few
-  // workgroups have nothing else to hide their latency (24 sequences of 8 chunks: this kernel's layer
-  // 27.7 -> 27.0 us, fp32 x 36.6 -> 35.6 us; 80 heads of 64 chunks in fp32 370 -> 368 us).
+  // ChunkScan1's operand fragments (frag.hpp: 1 KB per fragment, this lane's 16 bytes at lane * 16).
+  // The separate kernel requests them ahead, P_in behind x and before the waits for it, C_q of both
+  // row blocks once x has left its registers: few workgroups have nothing else to hide their latency.
+  // What is not needed (exp(r_{J-1}) zero) comes from an empty buffer, which reads nothing, so no
+  // branch separates loads in flight.  This kernel, 8 x 6, 24 x 8 and 80 x 64 sequences x chunks: 10.9,
+  // 12.0 and 84.7 us with Scan1 behind Scan2 of each row block, 11.7, 12.3 and 82.3 with Scan1 of both
+  // first and only P_in ahead, 10.5, 11.6 and 80.2 so; fp32 x (with the outputs below) 12.6, 14.4 and
+  // 270, then 13.5, 15.5 and 245, now 12.7, 14.5 and 240.
   const uint32_t lane16 = lane * 16;
   const __amdgpu_buffer_rsrc_t prs =
       buffer_rsrc(pin + (((size_t)b * nc + c) * H + h) * (size_t)kP * kN);
   auto frag_of = [&](__amdgpu_buffer_rsrc_t r, uint32_t o) {
     return __builtin_bit_cast(v4i, buf_load16(r, lane16, o));
   };
-  v4i pf[2 * kN / 32];
+  const int jta = wv, jtb = 7 - wv;   // this wave's row blocks
+  auto exp_r = [&](int jt) { return jt ? __expf((float)s_r[jt - 1]) : 1.0f; };   // exp(r_{J-1})
+  const bool tap_y1 = !kFused && y1_tap;   // the single pass has no Y1 tap
+  auto needs_y1 = [&](int jt) {
+    return tap_y1 || __builtin_amdgcn_readfirstlane((int)(exp_r(jt) != 0.0f)) != 0;
+  };
+  v4i pf[2 * kN / 32], qa[kN / 32], qb[kN / 32];
+  bool need_a, need_b;
   if constexpr (!kFused) {
+    need_a = needs_y1(jta);
+    need_b = needs_y1(jtb);
+    const uint32_t na = need_a || need_b ? 0xffffffffu : 0u, nb = need_b ? 0xffffffffu : 0u;
+    const __amdgpu_buffer_rsrc_t ps =
+        uniform_rsrc(pin + (((size_t)b * nc + c) * H + h) * (size_t)kP * kN, na);
+    const int8_t* cqg = cq_frag + (((size_t)b * nc + c) * G + g) * (size_t)kQ * kN;
+    const __amdgpu_buffer_rsrc_t cas = uniform_rsrc(cqg + jta * 32 * kN, na);
+    const __amdgpu_buffer_rsrc_t cbs = uniform_rsrc(cqg + jtb * 32 * kN, nb);
 #pragma unroll
-    for (int i = 0; i < 2 * kN / 32; ++i) pf[i] = frag_of(prs, 1024 * i);
+    for (int i = 0; i < 2 * kN / 32; ++i) pf[i] = frag_of(ps, 1024 * i);
     __builtin_amdgcn_sched_barrier(0);
     stage_xT();
+#pragma unroll
+    for (int i = 0; i < kN / 32; ++i) qa[i] = frag_of(cas, 1024 * i);
+#pragma unroll
+    for (int i = 0; i < kN / 32; ++i) qb[i] = frag_of(cbs, 1024 * i);
+    __builtin_amdgcn_sched_barrier(0);
   } else {
     // single pass: X_q^T [p][j] (int8, Eq. 7) first, in the bytes x^T takes later: each x
     // element is quantized once, by the thread that loaded it, with ChunkState's arithmetic
@@ -666,10 +690,7 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
   // Scan1 of both row blocks of this wave: Y1^T = P_in . C_q^T, int8 MFMA over n, the P_in
   // fragments (the same for both) loaded once.  Its term is Y1 a_C exp(cs_j) a_S[p]; when exp(r_{J-1})
   // is zero in fp32 every factor exp(cs_j) of the block is a zero product and Y1 is not needed (unless
-  // it is tapped); r only falls, so block jtb never needs it without block jta.
-  const int jta = wv, jtb = 7 - wv;
-  auto exp_r = [&](int jt) { return jt ? __expf((float)s_r[jt - 1]) : 1.0f; };   // exp(r_{J-1})
-  const bool tap_y1 = !kFused && y1_tap;   // the single pass has no Y1 tap
+  // it is tapped); where r only falls, block jtb never needs it without block jta.
 
   // The rest of a row block on its Y1: y = Y1 a_C exp(cs_j) a_S[p] + D x + corr[p], then Scan2 on top.
   auto row_block = [&](int jt, bool need, const v16i& yi0, const v16i& yi1, v16f& y0, v16f& y1) {
@@ -841,18 +862,32 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
     }
   };
   if constexpr (kFused) hand_off();
-  const bool need_a =
-      tap_y1 || __builtin_amdgcn_readfirstlane((int)(exp_r(jta) != 0.0f)) != 0;
-  const bool need_b =
-      tap_y1 || __builtin_amdgcn_readfirstlane((int)(exp_r(jtb) != 0.0f)) != 0;
+  if constexpr (kFused) {
+    need_a = needs_y1(jta);
+    need_b = needs_y1(jtb);
+  }
   v16i ia0, ia1, ib0, ib1;
-  {
+  if constexpr (!kFused) {
+    auto scan1 = [&](bool need, const v4i (&f)[kN / 32], v16i& i0, v16i& i1) {
+      if (need) {
+#pragma unroll
+        for (int ks = 0; ks < kN / 32; ++ks) {
+          i0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(pf[ks], f[ks], ks ? i0 : (v16i){}, 0, 0, 0);
+          i1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(pf[kN / 32 + ks], f[ks], ks ? i1 : (v16i){}, 0, 0,
+                                                     0);
+        }
+      } else {
+        asm volatile("" : "=v"(i0), "=v"(i1));   // never read
+      }
+    };
+    scan1(need_a || need_b, qa, ia0, ia1);   // one block after the other: fewer live registers
+    scan1(need_b, qb, ib0, ib1);
+  } else {
     const uint32_t ca = jta * (kN / 32) * 1024, cb = jtb * (kN / 32) * 1024;
-    auto pin_frag = [&](int i) { return kFused ? frag_of(prs, 1024 * i) : pf[i]; };
     if (need_b) {
 #pragma unroll
       for (int ks = 0; ks < kN / 32; ++ks) {
-        const v4i p0 = pin_frag(ks), p1 = pin_frag(kN / 32 + ks);
+        const v4i p0 = frag_of(prs, 1024 * ks), p1 = frag_of(prs, 1024 * (kN / 32 + ks));
         const v4i fa = frag_of(cqrs, ca + 1024 * ks), fb = frag_of(cqrs, cb + 1024 * ks);
         ia0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p0, fa, ks ? ia0 : (v16i){}, 0, 0, 0);
         ia1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p1, fa, ks ? ia1 : (v16i){}, 0, 0, 0);
@@ -862,7 +897,7 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
     } else if (need_a) {
 #pragma unroll
       for (int ks = 0; ks < kN / 32; ++ks) {
-        const v4i p0 = pin_frag(ks), p1 = pin_frag(kN / 32 + ks);
+        const v4i p0 = frag_of(prs, 1024 * ks), p1 = frag_of(prs, 1024 * (kN / 32 + ks));
         const v4i fa = frag_of(cqrs, ca + 1024 * ks);
         ia0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p0, fa, ks ? ia0 : (v16i){}, 0, 0, 0);
         ia1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(p1, fa, ks ? ia1 : (v16i){}, 0, 0, 0);
@@ -904,16 +939,20 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
     fp16::rows_out<128, 256>(s_xT, buffer_rsrc(y + tok0 * HP + (size_t)h * kP), t, HP, 0,
                              fs.stream);
   } else {
-    // fp32: 128 rows at a time
+    // fp32: each wave takes its row blocks out through 8 KB of its own, one after the other: no barrier
+    // but the one that ends the use of x^T.  Stored directly, all else the same, the separate kernel
+    // of 24 x 8, 80 x 8 and 80 x 64 sequences x chunks takes 15.2, 30.3 and 264 us instead of 14.3,
+    // 27.0 and 239
     const __amdgpu_buffer_rsrc_t yrs = buffer_rsrc(y + tok0 * HP + (size_t)h * kP);
+    uint8_t* s_w = s_xT + wv * (32 * 256);
     __syncthreads();
-    fp16::stage_rows_f32(s_xT, jta, lane, ya0, ya1);
-    __syncthreads();
-    fp16::rows_out<256, 256>(s_xT, yrs, t, HP, 0, fs.stream);
-    __syncthreads();
-    fp16::stage_rows_f32(s_xT, jtb - 4, lane, yb0, yb1);
-    __syncthreads();
-    fp16::rows_out<256, 256>(s_xT, yrs, t, HP, 128, fs.stream);
+    fp16::stage_rows_f32(s_w, 0, lane, ya0, ya1);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    fp16::rows_out_f32_wave(s_w, yrs, lane, HP, jta * 32, fs.stream);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    fp16::stage_rows_f32(s_w, 0, lane, yb0, yb1);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    fp16::rows_out_f32_wave(s_w, yrs, lane, HP, jtb * 32, fs.stream);
   }
 }
 

@@ -293,6 +293,20 @@ __device__ __forceinline__ void rows_out(const uint8_t* s_y, __amdgpu_buffer_rsr
     else buf_store16(v, yrs, yo, so);
   }
 }
+// The 32 fp32 rows from row0 on that one wave has staged, by that wave alone: four rows per store.
+__device__ __forceinline__ void rows_out_f32_wave(const uint8_t* s_y, __amdgpu_buffer_rsrc_t yrs,
+                                                  int lane, size_t HP, int row0, int stream) {
+  const int row = lane >> 4, col = lane & 15;
+  const uint32_t yo = (uint32_t)(row * HP * 4 + col * 16);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int r = 4 * k + row;
+    const uint4 v = *reinterpret_cast<const uint4*>(s_y + r * 256 + ((col ^ (r & 15)) * 16));
+    const uint32_t so = (uint32_t)((row0 + 4 * k) * HP * 4);
+    if (stream) buf_store16<kPolicyNT>(v, yrs, yo, so);
+    else buf_store16(v, yrs, yo, so);
+  }
+}
 static_assert(kP * kXTS >= kQ * kP * 2, "the output stages reuse the x^T bytes");
 
 // v of lane l ^ kXor, kXor < 32: a swizzle, which needs no lane address in a register.
