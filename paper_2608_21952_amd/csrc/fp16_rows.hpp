@@ -128,12 +128,10 @@ __device__ __forceinline__ float block_max(const float* cb_max_cg, int jt, int l
 // blocks on top.  Lane l: token row j = 32 jt + l % 32; register r of y0 / y1 holds channel p = 32
 // pt + 8 (r / 4) + 4 (l / 32) + r % 4.  cbrs: the chunk-group's fp32 CB blocks; cbm: block_max;
 // xg: fp32 x of the chunk and head (the D skip of an fp32 x is not rounded), token stride HP.
-// late() runs after the last CB load is issued: loads for what comes next belong there, since
-// vector loads complete in order.
-template <typename XT, typename F>
+template <typename XT>
 __device__ __forceinline__ void row_block(int jt, int lane, const Tables& T, const uint8_t* xT,
                                           __amdgpu_buffer_rsrc_t cbrs, float cbm, const XT* xg,
-                                          size_t HP, float Dh, v16f& y0, v16f& y1, F&& late) {
+                                          size_t HP, float Dh, v16f& y0, v16f& y1) {
   asm volatile("" : "+s"(jt) :: "memory");
   const int pc = lane & 31, half = lane >> 5;
   const uint32_t lane16 = lane * 16;
@@ -222,7 +220,6 @@ __device__ __forceinline__ void row_block(int jt, int lane, const Tables& T, con
 #pragma unroll
     for (int u = 0; u < 4; ++u) cur[u] = nx[u];
   }
-  late();
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
     const int i0 = jt * 32 + ks * 16 + 8 * half;

@@ -10,8 +10,8 @@
 // What bounds it: operand bytes through L1/L2 (CB 147 KB, C 64 KB, P_in per workgroup) beside the
 // x / y stream.  So each wave runs Scan1 of both of its row blocks from one load of P_in (64 KB
 // per workgroup; per row block, in fp32, it was 256 KB), its result seeds the Scan2 accumulators,
-// and CB blocks that decay makes zero weights of are not loaded.  124 VGPRs and 37 KB of LDS keep
-// four workgroups per CU (three before).  2.7B-shaped layer, slow heads included: 209 -> 99.5 us;
+// and CB blocks that decay makes zero weights of are not loaded.  At most 127 VGPRs and 37 KB of LDS
+// keep four workgroups per CU (three before).  2.7B-shaped layer, slow heads included: 209 -> 99.5 us;
 // 130M-shaped: 51.5 -> 33.8 us.
 #include "common.hpp"
 #include "fp16_rows.hpp"
@@ -128,9 +128,9 @@ __global__ __launch_bounds__(256, 4) void fp16_scan_kernel(
   }
 
   const XT* xg = x + tok0 * HP + (size_t)h * kP;
-  row_block<XT>(jta, lane, sm.tab, s_xT, cbrs, cma, xg, HP, Dh, ya0, ya1, [] {});
+  row_block<XT>(jta, lane, sm.tab, s_xT, cbrs, cma, xg, HP, Dh, ya0, ya1);
   if constexpr (sizeof(XT) == 4) cmb = block_max(cb_max + cg * frag::kCbBlocks, jtb, lane);
-  row_block<XT>(jtb, lane, sm.tab, s_xT, cbrs, cmb, xg, HP, Dh, yb0, yb1, [] {});
+  row_block<XT>(jtb, lane, sm.tab, s_xT, cbrs, cmb, xg, HP, Dh, yb0, yb1);
 
   // -- output: the two row blocks leave through the x^T bytes as whole token rows
   __syncthreads();
