@@ -28,8 +28,8 @@ MODULES = ("chunk_bmm", "chunk_state", "state_pass", "chunk_scan")
 # the single pass (fp16 x): ChunkState + StatePassing + ChunkScan in one kernel after ChunkBMM
 SINGLE = ("chunk_bmm", "single_pass")
 SOURCE = {"single_pass": "chunk_scan"}      # kernel -> source file of its HIP code
-# headers every kernel source compiles in: a change to them is a change to the kernel
-KERNEL_HEADERS = ("common.hpp", "exact_sum.hpp", "frag.hpp", "launch.hpp")
+# headers the layer's kernels compile in: a change to them is a change to the kernel
+KERNEL_HEADERS = ("common.hpp", "exact_sum.hpp", "fp16_rows.hpp", "frag.hpp", "launch.hpp")
 
 
 def _code_only(text: str) -> str:

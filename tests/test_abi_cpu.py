@@ -443,6 +443,22 @@ def test_traffic_source_hash_ignores_comments_only():
     assert bench.kernel_source_sha256("single_pass") is not None
 
 
+def test_traffic_source_hash_covers_the_headers():
+    """Every local header that the single pass's source includes, directly or not, counts."""
+    import re
+
+    import bench
+    csrc = os.path.join(ROOT, "paper_2608_21952_amd", "csrc")
+    seen, todo = set(), [bench.SOURCE["single_pass"] + ".hip"]
+    while todo:
+        with open(os.path.join(csrc, todo.pop()), encoding="utf-8") as f:
+            inc = re.findall(r'#include "([^"]+)"', f.read())
+        new = {n for n in inc if os.path.exists(os.path.join(csrc, n))} - seen
+        seen |= new
+        todo += sorted(new)
+    assert seen <= set(bench.KERNEL_HEADERS), seen - set(bench.KERNEL_HEADERS)
+
+
 def test_single_pass_selection_few_chunks(ssdi8):
     """Up to five chunks are a short chain: the single pass for few sequences; more chunks from 64
     sequences on."""
