@@ -166,9 +166,11 @@ typedef struct {
      sequence through the workspace (a flag per chunk; Eq. 9 applied in chunk order, so every
      integer result and y are bit-identical to the separate kernels).  The state_in_q tap is
      served by either path.  0: automatic (the single pass where it is the faster one, which
-     takes enough concurrent sequences to hide the serial hand-offs: batch * nheads >= 64 with
-     at least 4 chunks, or >= 48 with at least 32, or any number with 1 or 4 chunks); 1: always
-     the separate kernels; 2: the single pass whenever eligible.
+     takes a short chain or enough concurrent sequences to hide the serial hand-offs: any number
+     of sequences, batch * nheads, with 1, 4 or 5 chunks, fewer than 64 with 2 or 3, at least 64
+     with 6 or more, at least 48 with 32 or more); 1: always the separate kernels; 2: the single
+     pass whenever eligible.  Every path takes final_state_q == init_state_q (a sequence resumed
+     in place).
      With the single pass, events 1-2 of stage_events mark the end of ChunkBMM and 3-4 the
      single pass's own start and end. */
   int path;
@@ -271,7 +273,8 @@ ssdi8_status ssdi8_decode_step(int64_t batch, int64_t nheads, int64_t headdim, i
  * Sizes as ssdi8_ssd_chunk_scan; B and C are the unquantized fp16 (or fp32) tensors.  Scratch
  * goes through `workspace` (ssdi8_fp16_workspace_size).  stage_events: NULL or 5 hipEvent_t,
  * all recorded on `stream` between the kernels: before ChunkBMM, ChunkState, StatePassing and
- * ChunkScan and after ChunkScan.
+ * ChunkScan and after ChunkScan.  From 96 sequences (batch * nheads) on, ChunkState and
+ * StatePassing are one kernel: events 2 and 3 both follow it.
  */
 typedef struct {
   const void* x; int x_dtype;         /* [B,L,H,P] fp16 or fp32                                   */

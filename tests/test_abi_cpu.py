@@ -445,8 +445,6 @@ def test_traffic_source_hash_ignores_comments_only():
 
 def test_traffic_source_hash_covers_the_headers():
     """Every local header that the single pass's source includes, directly or not, counts."""
-    import re
-
     import bench
     csrc = os.path.join(ROOT, "paper_2608_21952_amd", "csrc")
     seen, todo = set(), [bench.SOURCE["single_pass"] + ".hip"]
