@@ -425,8 +425,14 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
 
   // The first off-diagonal ChunkScan2 block that row block jt runs: leading blocks whose every
   // fp16 weight rounds to zero are skipped (see the j-block).  jt itself when all are skipped.
-  auto first_block = [&](int jt) {
-    if (jt <= 0) return 0;
+  // `above`: byte J is non-zero where cs of a token of block J lies above r_{J-1} (or is NaN): a row
+  // factor e_j may then exceed 1 (dt or A outside the method's signs), and nothing is skipped.
+  auto rows_above = [&]() {
+    const float4 v = *reinterpret_cast<const float4*>(s_csr + 4 * lane);
+    return __ballot(!(v.x <= 0.0f && v.y <= 0.0f && v.z <= 0.0f && v.w <= 0.0f));
+  };
+  auto first_block = [&](int jt, uint64_t above) {
+    if (jt <= 0 || ((above >> (8 * jt)) & 0xffu)) return 0;
     const float4 ua = *reinterpret_cast<const float4*>(sm.umax);
     const float4 ub = *reinterpret_cast<const float4*>(sm.umax + 4);
     const float4 ra = *reinterpret_cast<const float4*>(s_R[jt - 1]);
@@ -460,7 +466,10 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
   auto hand_off = [&]() {
     // the first ChunkScan2 block of each row block, for the j-blocks after the hand-off's last
     // barrier (the tables are complete)
-    if (wv == 0 && lane < 8) sm.it0[lane] = first_block(lane);
+    if (wv == 0) {
+      const uint64_t above = rows_above();
+      if (lane < 8) sm.it0[lane] = first_block(lane, above);
+    }
     constexpr size_t kSlab = (size_t)kP * kN;
     constexpr int kPolicySc1 = 16;
     const int bh = b * H + h;
@@ -751,13 +760,13 @@ __global__ __launch_bounds__(256, 4) void chunk_scan_kernel(
           __builtin_amdgcn_readfirstlane((int)(s_csr[jt * 32 + 31] >= -kDiagSpan)) != 0;
       // Leading off-diagonal blocks whose every weight rounds to an fp16 zero are skipped (the
       // decay across the blocks between them and this row block has removed them): a weight of
-      // block it is q u_i e_j R[jt-1][it] with |q| <= 127 and e_j <= 1, below 127 2^-33 < 2^-26
-      // when max |u_i| R < 2^-33, and such a value rounds to zero.  it0 = the first block run.
+      // block it is q u_i e_j R[jt-1][it] with |q| <= 127 and e_j <= 1 (rows_above), below 127 2^-33 <
+      // 2^-26 when max |u_i| R < 2^-33, and such a value rounds to zero.  it0 = the first block run.
       int it0 = 0;
       if constexpr (kFused) {
         it0 = __builtin_amdgcn_readfirstlane(sm.it0[jt]);   // formed by the hand-off
       } else if (jt > 0) {
-        it0 = __builtin_amdgcn_readfirstlane(first_block(jt));
+        it0 = __builtin_amdgcn_readfirstlane(first_block(jt, rows_above()));
       }
       // W^T fragment of a 32x32 block (8 weights of this lane's token row per K-slice, as fp16)
       // times the x^T fragments of both channel tiles

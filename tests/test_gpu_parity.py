@@ -579,3 +579,33 @@ def test_non_finite_c_step_of_a_token(torch, ssdi8, dtype, path, value):
     assert not bool(got[:, list(rows)].isfinite().any())
     keep = [t for t in range(L) if t not in rows]
     assert torch.equal(got[:, keep], want[:, keep])
+
+
+@pytest.mark.parametrize("dtype,path", [(np.float16, "separate"), (np.float16, "single"),
+                                        (np.float32, "auto")])
+def test_decay_that_rises_again(torch, ssdi8, dtype, path):
+    """dt of both signs without the softplus: cs falls by 32 over one block of 32 tokens and rises by
+    32 over the next, so weights that are zero at that block's first row are of order one at its
+    last, and none of its blocks may be skipped.  The tokens in between have B = 0 (their weights
+    would leave the fp16 range)."""
+    say(f"decay that rises again {dtype.__name__} {path}")
+    rng = np.random.default_rng(9)
+    L, H = 256, 3
+    f = lambda *s: rng.standard_normal(s).astype(np.float16).astype(dtype)
+    inp = {"x": f(1, L, H, 64), "B": f(1, L, 1, 128), "C": f(1, L, 1, 128),
+           "dt_raw": np.full((1, L, H), 0.02, np.float32), "D": np.zeros(H, np.float32),
+           "A": np.array([-1.0, -0.9, -1.1], np.float32)}
+    inp["B"][:, 32:96] = 0
+    for lo, v in ((0, 0.05), (32, 1.0), (64, -1.0)):
+        inp["dt_raw"][:, lo:lo + 32] = v
+    cb = inp["C"][0, :, 0].astype(np.float64) @ inp["B"][0, :, 0].astype(np.float64).T
+    step = lambda a: np.full(1, np.abs(np.asarray(a, np.float64)).max() / 127, np.float32)
+    sc = {"alpha_B": step(inp["B"]), "alpha_C": step(inp["C"]), "alpha_CB": step(cb),
+          "alpha_Xs": np.ones((H, 64), np.float32), "alpha_S": np.ones((H, 64), np.float32),
+          "corr": np.zeros((H, 64), np.float32)}
+    g = run_layer(torch, ssdi8, inp, sc, dt_softplus=False, y_dtype=torch.float32, path=path)
+    ref = oq.ssdi8_forward(inp["x"], inp["dt_raw"], inp["A"], inp["B"], inp["C"], inp["D"],
+                           sc["corr"], sc, chunk=256, dt_softplus=False, want=("y64",))["y64"]
+    assert np.abs(ref[0, 88:96]).max() > 0.1      # the rows in question are not small
+    assert_close(g["y"], ref, "y")
+    assert_close(g["y"][:, 64:96], ref[:, 64:96], "y of the rows that rise")
