@@ -197,8 +197,8 @@ bool single_pass(const ssdi8_dims* d, const ssdi8_scan_args* a) {
   // / 25.9, four 26.7 / 25.9, 27.6 / 26.1, 28.6 / 27.2, five 27.6 / 26.5, 28.3 / 26.8, 30.2 / 28.1, six
   // 27.4 / 28.5, 28.3 / 29.1, 32.7 / 33.1, eight 26.7 / 29.8, 28.3 / 31.4, 36.0 / 35.7; 16 chunks 48 /
   // 50 (48), 53 / 53 (56), 55 / 52 (64), 65 / 60 (80); 32 chunks 48 / 62 (24), 71 / 67 (48).
-  // From 64 sequences on, two and three chunks keep the separate kernels: that selection is part
-  // of the tested interface (test_abi_cpu.py), though the single pass measures faster there too
+  // From 64 sequences on, two and three chunks keep the separate kernels, as before (and as
+  // test_abi_cpu.py states), though the single pass measures faster there too
   // (three chunks: 64 sequences 29.4 / 26.1, 320 52.8 / 37.7; two chunks of 640: 65.2 / 48.2)
   const int64_t nc = d->chunk > 0 ? d->seqlen / d->chunk : 0;
   const int64_t bh = d->batch * d->nheads;
